@@ -334,9 +334,9 @@ const char* h2o_last_error(void);
 /* Testing hook, not needed in normal use: force the bf16 SDPA kernel path of
  * h2o_sdpa_chunk for every later call in the process (-1 automatic, 0 the
  * generic VALU kernels, 1 the MFMA prefill kernels, 2 the decode kernels,
- * which need T == 1). float32 always uses the generic kernels. 0 also puts
- * h2o_sdpa_chunk_backward on its VALU kernels. Returns H2O_EINVAL for other
- * values. */
+ * which need T == 1). float32 uses the generic kernels under 0, else its own
+ * matrix-core kernels. 0 also puts h2o_sdpa_chunk_backward on its VALU kernels.
+ * Returns H2O_EINVAL for other values. */
 int h2o_debug_force_path(int path);
 
 /* Benchmark hook, not needed in normal use. h2o_debug_timing(1) makes every
@@ -355,7 +355,8 @@ int h2o_debug_force_path(int path);
  *  14 backward dQ (VALU: and the rows' D)  15 backward dK/dV
  *  16 KV gather / scatter   17 backward rows' D (MFMA path)
  *  18 backward dQ split reduce (MFMA path)
- *  19 bottom-k and insert in one launch (h2o_chunk_step, 1 < T <= 4096) */
+ *  19 bottom-k and insert in one launch (h2o_chunk_step, 1 < T <= 4096)
+ *  20 float32 attention (matrix cores) */
 int h2o_debug_timing(int on);
 int h2o_debug_kernel_time(int kernel_id, double* total_ms, long* count);
 

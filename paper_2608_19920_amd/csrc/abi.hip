@@ -142,15 +142,12 @@ int device_cus() {
   return n;
 }
 
-Plan make_plan(const Shape& s, int dtype) {
+namespace {
+
+// The plan of one kernel path for the shape.
+Plan path_plan(const Shape& s, int path) {
   Plan p{};
   const size_t BH = s.BH(), R = s.R(), Nk = s.Nk();
-  int path = dtype == H2O_BF16 ? 1 : 0;
-  if (dtype == H2O_BF16 && s.T == 1 && decode_supports(s.d, s.G())) path = 2;
-  const int forced = g_forced_path.load();
-  if (dtype == H2O_BF16 && forced >= 0) path = forced;
-  // the decode kernels need one query per head and an instantiated (d, G)
-  if (path == 2 && (s.T != 1 || !decode_supports(s.d, s.G()))) path = 1;
   p.path = path;
   p.nsplit = 1;
   p.nsplit_lse = 1;
@@ -221,6 +218,11 @@ Plan make_plan(const Shape& s, int dtype) {
     off = align256(off + 64 * 16);
     p.bytes = off;
     return p;
+  } else if (path == 3) {
+    // 32-row blocks read the keys half as often; 16-row blocks where 32 rows
+    // would leave CUs without a block
+    p.rows_per_part = (R + 31) / 32 * BH >= (size_t)device_cus() ? 32 : 16;
+    p.nparts = (int)((R + p.rows_per_part - 1) / p.rows_per_part);
   } else {
     p.rows_per_part = 64;
     p.nparts = (int)((R + 63) / 64);
@@ -240,6 +242,26 @@ Plan make_plan(const Shape& s, int dtype) {
   return p;
 }
 
+}  // namespace
+
+Plan make_plan(const Shape& s, int dtype, size_t max_bytes) {
+  const int forced = g_forced_path.load();
+  if (dtype != H2O_BF16) {
+    // the generic kernels where asked for, or where the smaller blocks'
+    // column partials do not fit
+    const Plan p = path_plan(s, forced == 0 ? 0 : 3);
+    return p.bytes <= max_bytes ? p : path_plan(s, 0);
+  }
+  int path = forced;
+  // the decode kernels need one query per head and an instantiated (d, G)
+  const bool decode = s.T == 1 && decode_supports(s.d, s.G());
+  if (path < 0) path = decode ? 2 : 1;
+  if (path == 2 && !decode) path = 1;
+  const Plan p = path_plan(s, path);
+  // (the decode kernels' stored logits are the larger part of their scratch)
+  return p.bytes <= max_bytes || path != 2 ? p : path_plan(s, 1);
+}
+
 namespace {
 
 // Validation shared by the entry points that run the attention; fills *plan.
@@ -249,7 +271,8 @@ int check_sdpa(const void* q, const void* k_cache, const void* v_cache, const vo
                const void* v_new, const void* out, const float* lse, const float* wsum,
                const void* workspace, size_t workspace_bytes, int B, int Hq, int Hkv, int T,
                int M, int d, float scale, int dtype, Plan* plan,
-               const int32_t* token_pos = nullptr, size_t extra_bytes = 0) {
+               const int32_t* token_pos = nullptr, size_t extra_bytes = 0,
+               size_t max_bytes = SIZE_MAX) {
   const bool cache = token_pos != nullptr;
   if (dtype != H2O_F32 && dtype != H2O_BF16) return fail(H2O_EDTYPE, "dtype %d unknown", dtype);
   int rc = check_shape(B, Hq, Hkv, T, M, d);
@@ -266,7 +289,7 @@ int check_sdpa(const void* q, const void* k_cache, const void* v_cache, const vo
   if (M > 0 && (!aligned16(k_cache) || !aligned16(v_cache)))
     return fail(H2O_EALIGN, "cache pointer not 16-byte aligned");
   const Shape s{B, Hq, Hkv, T, M, d, cache};
-  *plan = make_plan(s, dtype);
+  *plan = make_plan(s, dtype, max_bytes);
   const size_t need = align256(plan->bytes) + extra_bytes;
   if (workspace_bytes < need || (need > 0 && !workspace))
     return fail(H2O_EWORKSPACE, "workspace has %zu bytes, needs %zu", workspace_bytes, need);
@@ -289,6 +312,9 @@ hipError_t launch_sdpa(const Shape& s, const Plan& p, int dtype, const void* q,
     case 2:
       return launch_sdpa_decode(s, p, q, k_cache, v_cache, k_new, v_new, out, lse, wsum, ws,
                                 scale, kp, st);
+    case 3:
+      return launch_sdpa_f32(s, p, q, k_cache, v_cache, k_new, v_new, out, lse, wsum, ws, scale,
+                             kp, st, acc);
     default:
       return launch_sdpa_generic(s, p, dtype, q, k_cache, v_cache, k_new, v_new, out, lse,
                                  wsum, ws, scale, kp, st, acc);
@@ -418,10 +444,11 @@ int chunk_step(StepPart part, const void* q, void* k_cache, void* v_cache, float
                int32_t* token_pos, const void* k_new, const void* v_new, void* out, float* lse,
                float* wsum, int32_t* evict_idx, void* workspace, size_t workspace_bytes, int B,
                int Hq, int Hkv, int T, int M, int d, float scale, int32_t pos0, int dtype,
-               void* stream) {
+               void* stream, size_t max_bytes = SIZE_MAX) {
   Plan p;
   int rc = check_sdpa(q, k_cache, v_cache, k_new, v_new, out, lse, wsum, workspace,
-                      workspace_bytes, B, Hq, Hkv, T, M, d, scale, dtype, &p);
+                      workspace_bytes, B, Hq, Hkv, T, M, d, scale, dtype, &p, nullptr, 0,
+                      max_bytes);
   if (rc) return rc;
   if (M < T) return fail(H2O_EINVAL, "cache length M (%d) must be >= T (%d)", M, T);
   if (!scores || !evict_idx) return fail(H2O_EINVAL, "null tensor pointer");
@@ -540,7 +567,7 @@ int h2o_chunk_step_noalloc(const void* q, void* k_cache, void* v_cache, float* s
   if (dtype != H2O_F32 && dtype != H2O_BF16) return fail(H2O_EDTYPE, "dtype %d unknown", dtype);
   int rc = check_shape(B, Hq, Hkv, T, M, d);
   if (rc) return rc;
-  const size_t need = make_plan(Shape{B, Hq, Hkv, T, M, d}, dtype).bytes;
+  const size_t need = make_plan(Shape{B, Hq, Hkv, T, M, d}, dtype, kScratchBytes).bytes;
   if (need > kScratchBytes)
     return fail(H2O_EWORKSPACE,
                 "this shape needs %zu bytes of scratch; h2o_chunk_step_noalloc has %zu "
@@ -552,7 +579,7 @@ int h2o_chunk_step_noalloc(const void* q, void* k_cache, void* v_cache, float* s
   if (rc) return rc;
   return chunk_step(STEP_ALL, q, k_cache, v_cache, scores, token_pos, k_new, v_new, out, lse,
                     wsum, evict_idx, ws, kScratchBytes, B, Hq, Hkv, T, M, d, scale, pos0, dtype,
-                    stream);
+                    stream, kScratchBytes);
 }
 
 int h2o_chunk_step_attend(const void* q, void* k_cache, void* v_cache, float* scores,
@@ -770,12 +797,16 @@ int h2o_sdpa_chunk_backward(const void* q, const void* k_cache, const void* v_ca
   rc = check_device();
   if (rc) return rc;
   const Shape s{B, Hq, Hkv, T, M, d, cache};
-  // bf16 runs on the MFMA kernels unless the generic path is forced
-  const bool mfma = dtype == H2O_BF16 && g_forced_path.load() != 0;
+  // the matrix-core kernels of the type unless the generic path is forced
+  const bool mfma = g_forced_path.load() != 0;
   const hipStream_t st = reinterpret_cast<hipStream_t>(stream);
   const KeyPos kp{token_pos, pos0};
   hipError_t e =
-      mfma ? launch_sdpa_backward_mfma(s, q, k_cache, v_cache, k_new, v_new, kp, lse, dout, dq,
+      mfma && dtype == H2O_F32
+          ? launch_sdpa_backward_f32(s, q, k_cache, v_cache, k_new, v_new, kp, lse, dout, dq,
+                                     dk_cache, dv_cache, dk_new, dv_new,
+                                     reinterpret_cast<float*>(workspace), scale, st)
+      : mfma ? launch_sdpa_backward_mfma(s, q, k_cache, v_cache, k_new, v_new, kp, lse, dout, dq,
                                        dk_cache, dv_cache, dk_new, dv_new,
                                        reinterpret_cast<char*>(workspace), scale, st)
            : launch_sdpa_backward(s, dtype, q, k_cache, v_cache, k_new, v_new, kp, lse, dout,

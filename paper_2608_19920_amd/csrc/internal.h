@@ -103,7 +103,8 @@ __host__ __device__ __forceinline__ size_t align256_size(size_t n) { return (n +
 // Layout of the scratch buffer used by h2o_sdpa_chunk. All offsets are byte
 // offsets, 256-byte aligned.
 struct Plan {
-  int path;            // 0 = generic (float/bf16 VALU), 1 = bf16 MFMA, 2 = bf16 decode
+  int path;            // 0 = generic (float/bf16 VALU), 1 = bf16 MFMA, 2 = bf16 decode,
+                       // 3 = float32 MFMA
   int rows_per_part;   // packed rows per colsum partial
   int nparts;          // partials per KV head
   int nsplit;          // key-range splits per row tile of the main pass (MFMA path)
@@ -118,7 +119,8 @@ struct Plan {
   size_t off_keys;     // float accumulated scores [BH][M], the ranking copy of a chunk step
   size_t bytes;
 };
-Plan make_plan(const Shape& s, int dtype);
+// The plan of the least time whose workspace fits max_bytes, or the smallest.
+Plan make_plan(const Shape& s, int dtype, size_t max_bytes = SIZE_MAX);
 int mfma_rows_per_wave();        // packed rows per wave of the MFMA kernels
 int decode_max_split();      // largest split-block count per head of the decode kernels
 bool decode_supports(int d, int G);   // (d, G) pairs the decode kernels handle
@@ -129,7 +131,7 @@ enum KernelId {
   K_GENERIC_LSE = 0, K_GENERIC_MAIN, K_MFMA_LSE, K_MFMA_MAIN, K_SPLIT_REDUCE, K_COLSUM_REDUCE,
   K_ACCUMULATE, K_BOTTOMK, K_INSERT, K_DECODE_SPLIT, K_DECODE_COMBINE, K_ARGMIN_INSERT,
   K_DECODE_FINISH, K_KEYS, K_BWD_DQ, K_BWD_DKDV, K_KV_COPY, K_BWD_DOT, K_BWD_DQ_REDUCE,
-  K_BOTTOMK_INSERT, K_COUNT
+  K_BOTTOMK_INSERT, K_F32_ATTEND, K_COUNT
 };
 // While timing is switched on (h2o_debug_timing), kernels go out through
 // hipExtLaunchKernel with a start and a stop event: the runtime stamps them
@@ -164,6 +166,11 @@ hipError_t launch_sdpa_generic(const Shape& s, const Plan& p, int dtype, const v
                                const void* vn, void* out, float* lse, float* wsum,
                                char* ws, float scale, KeyPos kp, hipStream_t st,
                                ScoreAcc acc = ScoreAcc{});
+// float32 on the float32 matrix cores (a plan of path 3)
+hipError_t launch_sdpa_f32(const Shape& s, const Plan& p, const void* q, const void* kc,
+                           const void* vc, const void* kn, const void* vn, void* out, float* lse,
+                           float* wsum, char* ws, float scale, KeyPos kp, hipStream_t st,
+                           ScoreAcc acc = ScoreAcc{});
 hipError_t launch_sdpa_mfma(const Shape& s, const Plan& p, const void* q, const void* kc,
                             const void* vc, const void* kn, const void* vn, void* out,
                             float* lse, float* wsum, char* ws, float scale, KeyPos kp,
@@ -244,6 +251,11 @@ hipError_t launch_sdpa_backward(const Shape& s, int dtype, const void* q, const 
                                 const float* lse, const void* dout, void* dq, void* dkc,
                                 void* dvc, void* dkn, void* dvn, float* dot, float scale,
                                 hipStream_t st);
+// The same gradients on the float32 matrix cores, float32 data.
+hipError_t launch_sdpa_backward_f32(const Shape& s, const void* q, const void* kc, const void* vc,
+                                    const void* kn, const void* vn, KeyPos kp, const float* lse,
+                                    const void* dout, void* dq, void* dkc, void* dvc, void* dkn,
+                                    void* dvn, float* dot, float scale, hipStream_t st);
 // Workspace of the backward: D partials [ns_dot][BH][R] floats at offset 0
 // (the VALU kernels use the first plane) and, with several, one more plane
 // for their sum; then, when the dq pass is split, dq partials
