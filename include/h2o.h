@@ -356,7 +356,8 @@ int h2o_debug_force_path(int path);
  *  16 KV gather / scatter   17 backward rows' D (MFMA path)
  *  18 backward dQ split reduce (MFMA path)
  *  19 bottom-k and insert in one launch (h2o_chunk_step, 1 < T <= 4096)
- *  20 float32 attention (matrix cores) */
+ *  20 float32 attention (matrix cores)
+ *  21 decode argmin and insert (h2o_chunk_step, T == 1, long caches) */
 int h2o_debug_timing(int on);
 int h2o_debug_kernel_time(int kernel_id, double* total_ms, long* count);
 

@@ -23,9 +23,8 @@ namespace {
 
 constexpr int kThreads = 256;
 constexpr int kWaves = kThreads / 64;
-constexpr int kCombThreads = 1024;                       // threads of a combine block
 constexpr int kStep = 32;                                // cache slots per wave step
-constexpr int kMaxGD = 512;                              // G * D handled by these kernels
+constexpr int kMaxG = 8;                                 // query heads per KV head, at most
 constexpr int kMaxSplit = 64;                            // split blocks per head, at most
 
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
@@ -183,7 +182,47 @@ struct InsArgs {
   const bf16_t* vn;
   int32_t* evict_idx;     // [BH]
 };
-constexpr int kScPre = 16;   // scores per thread prefetched before the first K/V loads
+// The scan of the head's scores for its (score, slot)-smallest: kScVec 16-byte
+// loads per thread (4,096 slots a block) go out before the first K/V loads,
+// the rest of a longer row in rounds of as many. Rows of M % 4 != 0 slots, whose
+// starts are not 16-byte aligned, are read by single loads. (One load in flight per
+// thread past the first 4,096 slots made M = 32768 wait 112 times: the step
+// at B4 Hkv8 d128 166 us, 127 now.)
+constexpr int kScVec = 4;
+struct ScoreScan {
+  static constexpr int kSlots = 4 * kScVec * kThreads;   // slots per round
+  f32x4 v[kScVec];
+  __device__ __forceinline__ void load(const float* sc, int M, int base) {
+    const int tid = threadIdx.x;
+    if ((M & 3) == 0) {   // uniform
+#pragma unroll
+      for (int u = 0; u < kScVec; ++u) {
+        const int j = base + 4 * (tid + u * kThreads);
+        v[u] = j < M ? *reinterpret_cast<const f32x4*>(sc + j) : f32x4{0.f, 0.f, 0.f, 0.f};
+      }
+    } else {
+#pragma unroll
+      for (int u = 0; u < kScVec; ++u)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const int j = base + 4 * (tid + u * kThreads) + e;
+          v[u][e] = j < M ? sc[j] : 0.f;
+        }
+    }
+  }
+  // slots are visited in increasing order, so a strict < keeps the lowest of
+  // equal keys
+  __device__ __forceinline__ void take(int M, int base, uint32_t& bk, uint32_t& bj) const {
+#pragma unroll
+    for (int u = 0; u < kScVec; ++u)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const int j = base + 4 * ((int)threadIdx.x + u * kThreads) + e;
+        const uint32_t key = order_key(v[u][e]);
+        if (j < M && key < bk) { bk = key; bj = (uint32_t)j; }
+      }
+  }
+};
 
 template <int D, int G, bool CACHE, bool INS>
 __device__ __forceinline__ void split_body(
@@ -346,33 +385,23 @@ __device__ __forceinline__ void split_body(
 
   // INS: the scores and the chunk's rows are requested before the first K/V
   // loads, so the choice of the slot waits for them alone
-  float scp[INS ? kScPre : 1];
+  ScoreScan scan;
+  const float* sc_bh = INS ? ins.scores + bh * (size_t)M : nullptr;
   if (INS) {
-    const float* sc_bh = ins.scores + bh * (size_t)M;
-#pragma unroll
-    for (int u = 0; u < kScPre; ++u) {
-      const int j = tid + u * kThreads;
-      scp[u] = j < M ? sc_bh[j] : 0.f;
-    }
+    scan.load(sc_bh, M, 0);
 #pragma unroll
     for (int dh = 0; dh < DH; ++dh) knr[dh] = load16(ins.kn + bh * (size_t)D + 32 * dh + 8 * grp);
     vnr = load16(ins.vn + bh * (size_t)D + vcol);
   }
   issue(0, 0);
   if (INS) {
-    // (key, slot)-smallest, slots visited in increasing order per thread so
-    // that a strict < keeps the lowest slot among equal keys; the start
-    // (max key, slot 0) is a real pair whenever every key is the maximum
+    // (key, slot)-smallest; the start (max key, slot 0) is a real pair
+    // whenever every key is the maximum
     uint32_t bk = 0xFFFFFFFFu, bj = 0u;
-#pragma unroll
-    for (int u = 0; u < kScPre; ++u) {
-      const int j = tid + u * kThreads;
-      const uint32_t key = order_key(scp[u]);
-      if (j < M && key < bk) { bk = key; bj = (uint32_t)j; }
-    }
-    for (int j = tid + kScPre * kThreads; j < M; j += kThreads) {
-      const uint32_t key = order_key(ins.scores[bh * (size_t)M + j]);
-      if (key < bk) { bk = key; bj = (uint32_t)j; }
+    scan.take(M, 0, bk, bj);
+    for (int base = ScoreScan::kSlots; base < M; base += ScoreScan::kSlots) {
+      scan.load(sc_bh, M, base);
+      scan.take(M, base, bk, bj);
     }
     wave_argmin(bk, bj);
     if (lane == 0) { red_k[wave] = bk; red_j[wave] = bj; }
@@ -484,7 +513,6 @@ const void* split_kernel() {
 // Per-head merge of the split partials with the chunk's own key (column M),
 // shared by the combine kernel and the fused finish kernel so that both give
 // the same bits.
-constexpr int kMaxG = kMaxGD / 64;
 struct HeadStats {
   float lnew[kMaxG], lam[kMaxG], mfin[kMaxG], linv[kMaxG];
   float wt[kMaxSplit * kMaxG];   // weight of split s, head g: exp2(m_sg - mfin_g) or 0
@@ -498,7 +526,7 @@ struct HeadStats {
 // Without the chunk key (cache mode, has_chunk false) lnew is -inf, and a
 // query that sees no slot gets lam = +inf (every weight 0), linv = 0 and
 // lse = -inf.
-// The loads (head_stats_load, for wave g < G) and the arithmetic
+// The loads (head_stats_load) and the arithmetic
 // (head_stats_from) are separate so that a latency-bound kernel can issue the
 // loads together with its other early loads.
 template <int D>
@@ -509,9 +537,9 @@ struct StatIn {
 template <int D>
 __device__ __forceinline__ void head_stats_load(StatIn<D>& in, const bf16_t* q, const bf16_t* kn,
                                                 const float2* dstat, int Hq, int Hkv, int G,
-                                                int nsplit, size_t bh, bool has_chunk) {
+                                                int g, int nsplit, size_t bh, bool has_chunk) {
   const int b = (int)(bh / Hkv), h = (int)(bh % Hkv);
-  const int lane = threadIdx.x & 63, g = threadIdx.x >> 6;
+  const int lane = threadIdx.x & 63;
   in.st = lane < nsplit ? dstat[(bh * nsplit + lane) * G + g] : make_float2(-INFINITY, 0.f);
 #pragma unroll
   for (int i = 0; i < (D + 63) / 64; ++i) {
@@ -520,14 +548,13 @@ __device__ __forceinline__ void head_stats_load(StatIn<D>& in, const bf16_t* q, 
     in.kv[i] = has_chunk && dd < D ? kn[bh * D + dd] : (bf16_t)0;
   }
 }
-template <int D, int NT>
+template <int D>
 __device__ __forceinline__ void head_stats_from(HeadStats& hs, const StatIn<D>& in, int Hq,
-                                                int Hkv, int G, int nsplit, float c_log2,
+                                                int Hkv, int G, int g, int nsplit, float c_log2,
                                                 size_t bh, float* lse, bool has_chunk) {
-  static_assert(NT / 64 >= kMaxG, "one wave per query head of the group");
   const int b = (int)(bh / Hkv), h = (int)(bh % Hkv);
-  const int lane = threadIdx.x & 63, g = threadIdx.x >> 6;
-  if (g < G) {
+  const int lane = threadIdx.x & 63;
+  {
     const float2 st = in.st;
     float lnew = -INFINITY;
     if (has_chunk) {
@@ -555,18 +582,33 @@ __device__ __forceinline__ void head_stats_from(HeadStats& hs, const StatIn<D>& 
       if (lse) lse[(size_t)(b * Hq + h * G + g)] = any ? lm * kLn2 : -INFINITY;
     }
   }
-  __syncthreads();
 }
-template <int D, int NT>
-__device__ __forceinline__ void head_stats(HeadStats& hs, const bf16_t* q, const bf16_t* kn,
-                                           const float2* dstat, int Hq, int Hkv, int G,
-                                           int nsplit, float c_log2, size_t bh, float* lse,
-                                           bool has_chunk = true) {
-  StatIn<D> in;
-  if ((int)(threadIdx.x >> 6) < G)
-    head_stats_load<D>(in, q, kn, dstat, Hq, Hkv, G, nsplit, bh, has_chunk);
-  head_stats_from<D, NT>(hs, in, Hq, Hkv, G, nsplit, c_log2, bh, lse, has_chunk);
-}
+// All G heads by a block of NT threads: wave w takes heads w, w + NT / 64, ..
+// The inputs go into in[] with the caller's other early loads. Ends synced.
+template <int D, int G, int NT>
+struct StatsIn {
+  static constexpr int N = (G + NT / 64 - 1) / (NT / 64);
+  StatIn<D> in[N];
+  __device__ __forceinline__ void load(const bf16_t* q, const bf16_t* kn, const float2* dstat,
+                                       int Hq, int Hkv, int nsplit, size_t bh, bool has_chunk) {
+#pragma unroll
+    for (int n = 0; n < N; ++n) {
+      const int g = (int)(threadIdx.x >> 6) + n * (NT / 64);
+      if (g < G) head_stats_load<D>(in[n], q, kn, dstat, Hq, Hkv, G, g, nsplit, bh, has_chunk);
+    }
+  }
+  __device__ __forceinline__ void finish(HeadStats& hs, int Hq, int Hkv, int nsplit,
+                                         float c_log2, size_t bh, float* lse,
+                                         bool has_chunk) const {
+#pragma unroll
+    for (int n = 0; n < N; ++n) {
+      const int g = (int)(threadIdx.x >> 6) + n * (NT / 64);
+      if (g < G)
+        head_stats_from<D>(hs, in[n], Hq, Hkv, G, g, nsplit, c_log2, bh, lse, has_chunk);
+    }
+    __syncthreads();
+  }
+};
 
 // Output element c = g*D + dd of head bh: the chunk key's term plus the
 // weighted split O-partials in split order, normalised. The first PRE
@@ -581,72 +623,159 @@ __device__ __forceinline__ float out_elem(const HeadStats& hs, const bf16_t* vn,
 #pragma unroll
   for (int s = 0; s < PRE; ++s)
     if (s < nsplit) a = fmaf(pre[s], hs.wt[s * G + g], a);
+#pragma unroll 16
   for (int s = PRE; s < nsplit; ++s)
     a = fmaf(dO[(bh * nsplit + s) * (size_t)(G * D) + c], hs.wt[s * G + g], a);
   return a * hs.linv[g];
 }
 
-// out rows of the G query heads of head bh from the split O-partials.
-template <int D, int NT>
-__device__ __forceinline__ void head_out(const HeadStats& hs, const bf16_t* vn, const float* dO,
-                                         bf16_t* out, int Hq, int Hkv, int G, int nsplit,
-                                         size_t bh) {
-  const int b = (int)(bh / Hkv), h = (int)(bh % Hkv);
-  for (int c = threadIdx.x; c < G * D; c += NT) {
-    const float v = out_elem<D, 0>(hs, vn, dO, nullptr, G, nsplit, bh, c);
-    out[(size_t)(b * Hq + h * G) * D + c] = f32_to_bf16(v);
-  }
-}
-
-// Summed weight of cache slot j: sum_g exp2(logit_gj - lam_g), g in order.
-__device__ __forceinline__ float slot_weight(const HeadStats& hs, const float* lgb, int pitch,
-                                             int G, int j) {
-  float a = 0.f;
-  for (int g = 0; g < G; ++g) a += __builtin_amdgcn_exp2f(lgb[(size_t)g * pitch + j] - hs.lam[g]);
-  return a;
-}
 __device__ __forceinline__ float chunk_weight(const HeadStats& hs, int G) {
   float a = 0.f;
   for (int g = 0; g < G; ++g) a += __builtin_amdgcn_exp2f(hs.lnew[g] - hs.lam[g]);
   return a;
 }
+__device__ __forceinline__ bool lex_less(uint32_t ka, uint32_t ja, uint32_t kb, uint32_t jb) {
+  return ka < kb || (ka == kb && ja < jb);
+}
 
-// Block (x, bh) writes wsum for columns [x*kCols, +kCols) of head bh; block
-// x == 0 also writes out, lse and the chunk key's column (chunk mode: kn and
-// vn non-null, wsum rows of M + 1; cache mode: both null, rows of M). With
-// wsum null only out and lse are written (grid x = 1).
-constexpr int kCols = 1024;
-
-// With scores non-null (cache mode only) it also adds each slot's summed
-// weight to its score: scores[j] += wsum[j], one float32 addition; with
-// ins_idx non-null the head's slot ins_idx[bh] (just inserted, by the fused
-// insert-first split) takes 0 + wsum[j] instead.
-template <int D>
+// Blocks x < nx write wsum for the slots [x*kCombSlots, +kCombSlots) of head
+// bh, wsum[j] = sum_g exp2(logit_gj - lam_g) with g in order: four consecutive
+// slots per thread, their logits and scores requested with the inputs of the
+// head statistics, before anything is waited for. The other blocks write out
+// and lse (out non-null), one element of out per thread, and the first of them
+// the chunk key's column (chunk mode: kn and vn non-null, wsum rows of M + 1;
+// cache mode: both null, rows of M). With wsum null, nx is 0.
+// With scores non-null each slot's summed weight is added to its score, one
+// float32 addition; with ins_idx non-null the head's slot ins_idx[bh] (just
+// inserted, by the fused insert-first split) takes 0 + wsum[j] instead.
+// CAND: the block also leaves the (key, slot)-smallest of its updated scores
+// in the first two logits of its slots, which it alone has read.
+// Bound by latency (statistics, then exp2 and the stores). Blocks of 1,024
+// threads with one slot each, out written by a block that also had slots:
+// 13.2 us at B4 Hkv8 G4 M32768, 7.0 like this (256 or 1,024 threads: 7.4, 7.3).
+constexpr int kCombThreads = 512;
+constexpr int kCombSlots = 4 * kCombThreads;
+template <int D, int G, bool CAND>
 __global__ __launch_bounds__(kCombThreads) void decode_combine(
     const bf16_t* __restrict__ q, const bf16_t* __restrict__ kn, const bf16_t* __restrict__ vn,
-    int Hq, int Hkv, int M, int nsplit, float c_log2, const float* __restrict__ logits,
+    int Hq, int Hkv, int M, int nx, int nsplit, float c_log2, float* __restrict__ logits,
     const float2* __restrict__ dstat, const float* __restrict__ dO, bf16_t* __restrict__ out,
     float* __restrict__ lse, float* __restrict__ wsum, float* __restrict__ scores,
     const int32_t* __restrict__ ins_idx) {
+  constexpr int NT = kCombThreads;
   __shared__ HeadStats hs;
-  const int G = Hq / Hkv;
+  __shared__ uint32_t red_k[NT / 64], red_j[NT / 64];
   const size_t bh = blockIdx.y;
+  const int tid = threadIdx.x;
   const bool has_chunk = kn != nullptr;
-  head_stats<D, kCombThreads>(hs, q, kn, dstat, Hq, Hkv, G, nsplit, c_log2, bh,
-                          blockIdx.x == 0 ? lse : nullptr, has_chunk);
-  if (blockIdx.x == 0) head_out<D, kCombThreads>(hs, vn, dO, out, Hq, Hkv, G, nsplit, bh);
-  if (!wsum) return;   // out and lse only (the attend half of a step)
+  StatsIn<D, G, NT> sin;
+  sin.load(q, kn, dstat, Hq, Hkv, nsplit, bh, has_chunk);
   float* w = wsum + bh * (size_t)(M + (has_chunk ? 1 : 0));
-  const float* lgb = logits + bh * (size_t)G * logit_pitch(M);
-  const int c0 = blockIdx.x * kCols, c1 = min(M, c0 + kCols);
-  float* sc = scores ? scores + bh * (size_t)M : nullptr;
-  const int ins = ins_idx ? ins_idx[bh] : -1;
-  for (int j = c0 + threadIdx.x; j < c1; j += kCombThreads) {
-    const float wj = slot_weight(hs, lgb, logit_pitch(M), G, j);
-    w[j] = wj;
-    if (sc) sc[j] = (j == ins ? 0.f : sc[j]) + wj;
+  if ((int)blockIdx.x >= nx) {
+    const int part = (int)blockIdx.x - nx, c = part * NT + tid;
+    sin.finish(hs, Hq, Hkv, nsplit, c_log2, bh, out && part == 0 ? lse : nullptr, has_chunk);
+    if (out && c < G * D) {
+      const int b = (int)(bh / Hkv), h = (int)(bh % Hkv);
+      out[(size_t)(b * Hq + h * G) * D + c] =
+          f32_to_bf16(out_elem<D, 0>(hs, vn, dO, nullptr, G, nsplit, bh, c));
+    }
+    if (wsum && has_chunk && part == 0 && tid == 0) w[M] = chunk_weight(hs, G);
+    return;
   }
-  if (has_chunk && blockIdx.x == 0 && threadIdx.x == 0) w[M] = chunk_weight(hs, G);
+  const int pitch = logit_pitch(M), c0 = blockIdx.x * kCombSlots, j0 = c0 + 4 * tid;
+  float* lgb = logits + bh * (size_t)G * pitch;
+  float* sc = scores ? scores + bh * (size_t)M : nullptr;
+  const bool sc16 = (M & 3) == 0;     // score rows start 16-byte aligned
+  f32x4 lg[G], sv = {0.f, 0.f, 0.f, 0.f};
+  int ins = -1;
+  if (j0 < M) {   // a logit row is padded to a multiple of 4 slots
+#pragma unroll
+    for (int g = 0; g < G; ++g) lg[g] = *reinterpret_cast<const f32x4*>(lgb + (size_t)g * pitch + j0);
+    if (sc && sc16) {
+      sv = *reinterpret_cast<const f32x4*>(sc + j0);
+    } else if (sc) {
+#pragma unroll
+      for (int r = 0; r < 4; ++r) sv[r] = sc[min(j0 + r, M - 1)];
+    }
+    if (ins_idx) ins = ins_idx[bh];
+  }
+  sin.finish(hs, Hq, Hkv, nsplit, c_log2, bh, nullptr, has_chunk);
+  // the lowest slot of equal keys: slots in increasing order under a strict <
+  uint32_t bk = 0xFFFFFFFFu, bj = (uint32_t)c0;
+  if (j0 < M) {
+    f32x4 wv, sa;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      float a = 0.f;
+#pragma unroll
+      for (int g = 0; g < G; ++g) a += __builtin_amdgcn_exp2f(lg[g][r] - hs.lam[g]);
+      wv[r] = a;
+      sa[r] = (j0 + r == ins ? 0.f : sv[r]) + a;
+      if (CAND) {
+        const uint32_t key = order_key(sa[r]);
+        if (j0 + r < M && key < bk) { bk = key; bj = (uint32_t)(j0 + r); }
+      }
+    }
+    if (!has_chunk && sc16) {
+      *reinterpret_cast<f32x4*>(w + j0) = wv;
+    } else {
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+        if (j0 + r < M) w[j0 + r] = wv[r];
+    }
+    if (sc && sc16) {
+      *reinterpret_cast<f32x4*>(sc + j0) = sa;
+    } else if (sc) {
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+        if (j0 + r < M) sc[j0 + r] = sa[r];
+    }
+  }
+  if constexpr (CAND) {
+    wave_argmin(bk, bj);
+    if ((tid & 63) == 0) { red_k[tid >> 6] = bk; red_j[tid >> 6] = bj; }
+    __syncthreads();
+    if (tid == 0) {
+      for (int v = 1; v < NT / 64; ++v)
+        if (lex_less(red_k[v], red_j[v], bk, bj)) { bk = red_k[v]; bj = red_j[v]; }
+      *reinterpret_cast<uint2*>(lgb + c0) = make_uint2(bk, bj);
+    }
+  }
+}
+
+// The end of a token step whose combine ran with CAND: one wave per head takes
+// the smallest of the blocks' candidates and inserts the chunk there.
+__global__ __launch_bounds__(64) void decode_insert(
+    bf16_t* __restrict__ kc, bf16_t* __restrict__ vc, const bf16_t* __restrict__ kn,
+    const bf16_t* __restrict__ vn, int G, int D, int M, const float* __restrict__ logits,
+    const float* __restrict__ wsum, float* __restrict__ scores, int32_t* __restrict__ token_pos,
+    int32_t* __restrict__ evict_idx, int32_t pos0) {
+  const size_t bh = blockIdx.x;
+  const int lane = threadIdx.x;
+  const float* cand = logits + bh * (size_t)G * logit_pitch(M);
+  const float wnew = wsum[bh * (size_t)(M + 1) + M];
+  const bool copy = lane < D / 8;
+  u32x4 krow = {0u, 0u, 0u, 0u}, vrow = krow;
+  if (copy) {
+    krow = load16(kn + bh * D + 8 * lane);
+    vrow = load16(vn + bh * D + 8 * lane);
+  }
+  uint32_t bk = 0xFFFFFFFFu, bj = 0u;
+  for (int x = lane; x * kCombSlots < M; x += 64) {
+    const uint2 c = *reinterpret_cast<const uint2*>(cand + (size_t)x * kCombSlots);
+    if (lex_less(c.x, c.y, bk, bj)) { bk = c.x; bj = c.y; }
+  }
+  wave_argmin(bk, bj);
+  const size_t slot = bh * (size_t)M + bj;
+  if (lane == 0) {
+    evict_idx[bh] = (int32_t)bj;
+    scores[slot] = wnew;
+    if (token_pos) token_pos[slot] = pos0;
+  }
+  if (copy) {
+    *reinterpret_cast<u32x4*>(kc + slot * D + 8 * lane) = krow;
+    *reinterpret_cast<u32x4*>(vc + slot * D + 8 * lane) = vrow;
+  }
 }
 
 // Fused end of a token step, one block per head: the combine above, then
@@ -665,10 +794,6 @@ __global__ __launch_bounds__(kCombThreads) void decode_combine(
 constexpr int kFinThreads = 1024;
 constexpr int kFinVec = 4;                          // consecutive slots per thread and pass
 constexpr int kFinPass = kFinThreads * kFinVec;     // slots per pass
-
-__device__ __forceinline__ bool lex_less(uint32_t ka, uint32_t ja, uint32_t kb, uint32_t jb) {
-  return ka < kb || (ka == kb && ja < jb);
-}
 
 // With OUT false the block skips out and lse (written by decode_combine in
 // an attend call): the eviction half of the step.
@@ -723,10 +848,10 @@ __global__ __launch_bounds__(kFinThreads) void decode_finish(
 #pragma unroll
   for (int s = 0; s < kPre; ++s)
     pre[s] = has_c && s < nsplit ? dO[(bh * nsplit + s) * (size_t)(G * D) + tid] : 0.f;
-  StatIn<D> sin;
-  if (wave < G) head_stats_load<D>(sin, q, kn, dstat, Hq, Hkv, G, nsplit, bh, true);
+  StatsIn<D, G, NT> sin;
+  sin.load(q, kn, dstat, Hq, Hkv, nsplit, bh, true);
   load_pass(0);
-  head_stats_from<D, NT>(hs, sin, Hq, Hkv, G, nsplit, c_log2, bh, OUT ? lse : nullptr, true);
+  sin.finish(hs, Hq, Hkv, nsplit, c_log2, bh, OUT ? lse : nullptr, true);
   if (has_c) {
     const float v = out_elem<D, kPre>(hs, vn, dO, pre, G, nsplit, bh, tid);
     const int b = (int)(bh / Hkv), h = (int)(bh % Hkv);
@@ -867,11 +992,27 @@ hipError_t launch_split(hipStream_t st, int BH, const void* q, const void* kc, c
 
 int decode_max_split() { return kMaxSplit; }
 
-// The decode kernels are instantiated for these (d, G) pairs.
-bool decode_supports(int d, int G) {
-  return (d == 64 && (G == 1 || G == 2 || G == 4 || G == 8)) ||
-         (d == 128 && (G == 1 || G == 2 || G == 4));
+// The decode kernels are instantiated for d = 64 and 128 and every group of 1
+// to 8 query heads. (The prefill kernels, which take the rest, pad the G rows
+// of a head to 128: GQA 7:1 at B2 Hkv4 d128 M16384 84 us a step
+// there, 25 here.)
+bool decode_supports(int d, int G) { return (d == 64 || d == 128) && G >= 1 && G <= kMaxG; }
+
+namespace {
+// f(integral_constant<d>, integral_constant<G>) for a supported pair.
+template <int V>
+struct IntC { static constexpr int value = V; };
+template <int D, int G = 1, class F>
+hipError_t with_group(int g, F&& f) {
+  if (g == G) return f(IntC<D>{}, IntC<G>{});
+  if constexpr (G < kMaxG) return with_group<D, G + 1>(g, f);
+  else return hipErrorInvalidValue;
 }
+template <class F>
+hipError_t with_shape(const Shape& s, F&& f) {
+  return s.d == 64 ? with_group<64>(s.G(), f) : with_group<128>(s.G(), f);
+}
+}  // namespace
 
 namespace {
 
@@ -885,23 +1026,34 @@ hipError_t launch_decode_split(const Shape& s, const Plan& p, const void* q, con
   float* sink = reinterpret_cast<float*>(ws + p.off_parts);
   *ns = 0;
   if (s.M == 0) return hipSuccess;
-  const int G = s.G();
-  hipError_t e = hipErrorInvalidValue;
-#define H2O_SPLIT(DD, GG) \
-  e = launch_split<DD, GG>(st, s.BH(), q, kc, vc, s.Hq, s.Hkv, s.M, c, logits, dstat, dO, sink, \
-                           kp, ns, ins)
-  if (s.d == 64) {
-    if (G == 1) H2O_SPLIT(64, 1);
-    else if (G == 2) H2O_SPLIT(64, 2);
-    else if (G == 4) H2O_SPLIT(64, 4);
-    else if (G == 8) H2O_SPLIT(64, 8);
-  } else {
-    if (G == 1) H2O_SPLIT(128, 1);
-    else if (G == 2) H2O_SPLIT(128, 2);
-    else if (G == 4) H2O_SPLIT(128, 4);
-  }
-#undef H2O_SPLIT
-  return e;
+  return with_shape(s, [&](auto d, auto g) {
+    return launch_split<d.value, g.value>(st, s.BH(), q, kc, vc, s.Hq, s.Hkv, s.M, c, logits,
+                                          dstat, dO, sink, kp, ns, ins);
+  });
+}
+
+}  // namespace
+
+namespace {
+
+// The combine kernel; chunk mode where kn is non-null. out null: no out and
+// lse; wsum null: nothing else. cand: leave the blocks' eviction candidates.
+hipError_t launch_combine(const Shape& s, const Plan& p, int ns, const void* q, const void* kn,
+                          const void* vn, void* out, float* lse, float* wsum, float* scores,
+                          const int32_t* ins_idx, bool cand, char* ws, float c, hipStream_t st) {
+  const int nx = wsum ? (s.M + kCombSlots - 1) / kCombSlots : 0;
+  const dim3 grid(nx + (out ? (s.G() * s.d + kCombThreads - 1) / kCombThreads : 1), s.BH());
+  return with_shape(s, [&](auto d, auto g) {
+    auto go = [&](auto kern) {
+      return launch_kernel(K_DECODE_COMBINE, kern, grid, dim3(kCombThreads), st, (const bf16_t*)q,
+                           (const bf16_t*)kn, (const bf16_t*)vn, s.Hq, s.Hkv, s.M, nx, ns, c,
+                           (float*)(ws + p.off_logits), (const float2*)(ws + p.off_stats),
+                           (const float*)(ws + p.off_opart), (bf16_t*)out, lse, wsum, scores,
+                           ins_idx);
+    };
+    return cand ? go(decode_combine<d.value, g.value, true>)
+                : go(decode_combine<d.value, g.value, false>);
+  });
 }
 
 }  // namespace
@@ -914,15 +1066,9 @@ hipError_t launch_sdpa_decode(const Shape& s, const Plan& p, const void* q, cons
   int ns = 0;
   hipError_t e = launch_decode_split(s, p, q, kc, vc, ws, c, kp, st, &ns);
   if (e != hipSuccess) return e;
-  const dim3 cgrid(s.M > 0 ? (s.M + kCols - 1) / kCols : 1, s.BH());
-  auto combine = s.d == 64 ? decode_combine<64> : decode_combine<128>;
   const bool chunk = !s.cache_only;
-  return launch_kernel(K_DECODE_COMBINE, combine, cgrid, dim3(kCombThreads), st, (const bf16_t*)q,
-                       chunk ? (const bf16_t*)kn : nullptr, chunk ? (const bf16_t*)vn : nullptr,
-                       s.Hq, s.Hkv, s.M, ns, c,
-                       (const float*)(ws + p.off_logits), (const float2*)(ws + p.off_stats),
-                       (const float*)(ws + p.off_opart), (bf16_t*)out, lse, wsum,
-                       chunk ? nullptr : scores_acc, (const int32_t*)nullptr);
+  return launch_combine(s, p, ns, q, chunk ? kn : nullptr, chunk ? vn : nullptr, out, lse, wsum,
+                        chunk ? nullptr : scores_acc, nullptr, false, ws, c, st);
 }
 
 hipError_t launch_decode_step_insert_first(const Shape& s, const Plan& p, const void* q,
@@ -936,23 +1082,31 @@ hipError_t launch_decode_step_insert_first(const Shape& s, const Plan& p, const 
       s, p, q, kc, vc, ws, c, KeyPos{token_pos, pos0}, st, &ns,
       InsArgs{scores, (const bf16_t*)kn, (const bf16_t*)vn, evict_idx});
   if (e != hipSuccess) return e;
-  const dim3 cgrid((s.M + kCols - 1) / kCols, s.BH());
-  auto combine = s.d == 64 ? decode_combine<64> : decode_combine<128>;
-  return launch_kernel(K_DECODE_COMBINE, combine, cgrid, dim3(kCombThreads), st, (const bf16_t*)q,
-                       (const bf16_t*)nullptr, (const bf16_t*)nullptr, s.Hq, s.Hkv, s.M, ns, c,
-                       (const float*)(ws + p.off_logits), (const float2*)(ws + p.off_stats),
-                       (const float*)(ws + p.off_opart), (bf16_t*)out, lse, wsum, scores,
-                       (const int32_t*)evict_idx);
+  return launch_combine(s, p, ns, q, nullptr, nullptr, out, lse, wsum, scores, evict_idx, false,
+                        ws, c, st);
 }
 
 namespace {
 
-// The finish kernel for this (d, G); out_too selects the fused form.
+// The end of a token step: one finish block per head where it takes its slots in
+// one pass, else the combine over all CUs and one wave per head for the
+// choice and the insert. (M = 8192, GQA 7:1, B2 Hkv4 d128:
+// finish 12.3 us, the two kernels 9.9 - an event pair shows no less than 4 for
+// a kernel; at one pass, B8 Hkv8 d64 M4096, 5.4 against 8.5.)
+// out_too: out and lse as well (the fused form).
 hipError_t launch_finish(const Shape& s, const Plan& p, bool out_too, int ns, const void* q,
                          void* kc, void* vc, const void* kn, const void* vn, void* out,
                          float* lse, float* wsum, float* scores, int32_t* token_pos,
                          int32_t* evict_idx, int32_t pos0, char* ws, float c, hipStream_t st) {
-  const int G = s.G();
+  if (s.M > kFinPass) {
+    const hipError_t e = launch_combine(s, p, ns, q, kn, vn, out_too ? out : nullptr, lse, wsum,
+                                        scores, nullptr, true, ws, c, st);
+    if (e != hipSuccess) return e;
+    return launch_kernel(K_DECODE_INSERT, decode_insert, dim3(s.BH()), dim3(64), st, (bf16_t*)kc,
+                         (bf16_t*)vc, (const bf16_t*)kn, (const bf16_t*)vn, s.G(), s.d, s.M,
+                         (const float*)(ws + p.off_logits), (const float*)wsum, scores, token_pos,
+                         evict_idx, pos0);
+  }
   auto go = [&](auto kern) {
     return launch_kernel(K_DECODE_FINISH, kern, dim3(s.BH()), dim3(kFinThreads), st,
                          (const bf16_t*)q, (bf16_t*)kc, (bf16_t*)vc, (const bf16_t*)kn,
@@ -961,37 +1115,21 @@ hipError_t launch_finish(const Shape& s, const Plan& p, bool out_too, int ns, co
                          (const float*)(ws + p.off_opart), (bf16_t*)out, lse, wsum, scores,
                          token_pos, evict_idx, pos0);
   };
-#define H2O_FIN(DD, GG) \
-  return out_too ? go(decode_finish<DD, GG, true>) : go(decode_finish<DD, GG, false>)
-  if (s.d == 64) {
-    if (G == 1) H2O_FIN(64, 1);
-    if (G == 2) H2O_FIN(64, 2);
-    if (G == 4) H2O_FIN(64, 4);
-    if (G == 8) H2O_FIN(64, 8);
-  } else {
-    if (G == 1) H2O_FIN(128, 1);
-    if (G == 2) H2O_FIN(128, 2);
-    if (G == 4) H2O_FIN(128, 4);
-  }
-#undef H2O_FIN
-  return hipErrorInvalidValue;
+  return with_shape(s, [&](auto d, auto g) {
+    return out_too ? go(decode_finish<d.value, g.value, true>)
+                   : go(decode_finish<d.value, g.value, false>);
+  });
 }
 
 // The split count the split kernel used for this shape (chunk mode).
 int split_count_for(const Shape& s) {
-  const int G = s.G();
-  if (s.M == 0) return 0;
-  if (s.d == 64) {
-    if (G == 1) return split_count<64, 1, false>(s.M, s.BH());
-    if (G == 2) return split_count<64, 2, false>(s.M, s.BH());
-    if (G == 4) return split_count<64, 4, false>(s.M, s.BH());
-    if (G == 8) return split_count<64, 8, false>(s.M, s.BH());
-  } else {
-    if (G == 1) return split_count<128, 1, false>(s.M, s.BH());
-    if (G == 2) return split_count<128, 2, false>(s.M, s.BH());
-    if (G == 4) return split_count<128, 4, false>(s.M, s.BH());
-  }
-  return 0;
+  int ns = 0;
+  if (s.M > 0)
+    (void)with_shape(s, [&](auto d, auto g) {
+      ns = split_count<d.value, g.value, false>(s.M, s.BH());
+      return hipSuccess;
+    });
+  return ns;
 }
 
 }  // namespace
@@ -1003,13 +1141,7 @@ hipError_t launch_decode_attend(const Shape& s, const Plan& p, const void* q, co
   int ns = 0;
   hipError_t e = launch_decode_split(s, p, q, kc, vc, ws, c, KeyPos{nullptr, 0}, st, &ns);
   if (e != hipSuccess) return e;
-  auto combine = s.d == 64 ? decode_combine<64> : decode_combine<128>;
-  return launch_kernel(K_DECODE_COMBINE, combine, dim3(1, s.BH()), dim3(kCombThreads), st,
-                       (const bf16_t*)q, (const bf16_t*)kn, (const bf16_t*)vn, s.Hq, s.Hkv,
-                       s.M, ns, c, (const float*)(ws + p.off_logits),
-                       (const float2*)(ws + p.off_stats), (const float*)(ws + p.off_opart),
-                       (bf16_t*)out, lse, (float*)nullptr, (float*)nullptr,
-                       (const int32_t*)nullptr);
+  return launch_combine(s, p, ns, q, kn, vn, out, lse, nullptr, nullptr, nullptr, false, ws, c, st);
 }
 
 hipError_t launch_decode_evict(const Shape& s, const Plan& p, const void* q, void* kc, void* vc,
