@@ -144,19 +144,24 @@ int device_cus() {
 
 namespace {
 
-// The plan of one kernel path for the shape.
-Plan path_plan(const Shape& s, int path) {
+// The plan of one kernel path for the shape; lean: the prefill kernels without
+// key splits (the least workspace).
+Plan path_plan(const Shape& s, int path, bool lean = false) {
   Plan p{};
   const size_t BH = s.BH(), R = s.R(), Nk = s.Nk();
   p.path = path;
   p.nsplit = 1;
   p.nsplit_lse = 1;
   p.parts_ld = (int)Nk;
-  if (path == 1) {
+  if (path == 1 && lean) {
+    p.main_waves = p.lse_waves = s.d == 128 ? 8 : 4;
+    p.rows_per_part = p.main_waves * mfma_rows_per_wave();
+    p.nparts = (int)((R + p.rows_per_part - 1) / p.rows_per_part);
+    p.parts_ld = (int)((Nk + 31) / 32 * 32);
+  } else if (path == 1) {
     // Split the key range of each row tile when there are too few blocks to
-    // fill the CUs (a round: the blocks resident at once; the main pass fits
-    // two 4-wave or one 8-wave block per CU, the lighter lse pass four
-    // 4-wave or two 8-wave blocks). Keep at least 8 key tiles per split.
+    // fill the CUs (a round: the blocks resident at once). At least 8 key
+    // tiles per split, at most 8 splits.
     const long long ntiles = (Nk + 31) / 32;
     const long long cus = device_cus();
     auto pick = [&](long long nb, long long target, long long maxs) {
@@ -165,35 +170,59 @@ Plan path_plan(const Shape& s, int path) {
       if (ns > maxs) ns = maxs;
       return (int)(ns < 1 ? 1 : ns);
     };
-    // main-pass blocks of `waves` waves: their row-tile count and split
-    auto main_grid = [&](int waves, long long& nrt_w, int& ns_w) {
-      const long long rows_w = (long long)waves * mfma_rows_per_wave();
-      const long long round = cus * (8 / waves);
-      nrt_w = ((long long)R + rows_w - 1) / rows_w;
-      const long long nb = nrt_w * (long long)BH;
-      ns_w = pick(nb, round, 8);
-      // Between one and two rounds the second round is partly filled and
-      // runs at the pace of its fullest CUs; halved blocks shorten it (896
-      // row tiles of 128 rows at GQA 7:1: 1,150 -> 1,030 us for the pass,
-      // 22 us for the O partials' reduce).
-      if (ns_w == 1 && nb > round && nb < 2 * round && ntiles >= 16) ns_w = 2;
-      return nb * ns_w % round == 0;   // whole rounds
-    };
-    // 8-wave blocks where they fill whole rounds (two blocks sharing a CU
-    // advance unevenly; one block per CU leaves CUs idle in a partial round)
+    // The main pass: the block shape (4 waves, or 8 at d = 128) and split of
+    // least estimated time. us[k-1]: microseconds per key tile of a block
+    // that shares its CU with k - 1 others; a round takes every block's tiles
+    // at full residency, the last one at what is left, and about 8 us to start
+    // and end; the O partials of several splits are written, read and reduced
+    // (2 us and a byte of them in 1 / 3 TB/s).
+    // Fitted on sweeps of the split at B1 Hkv8 M8192 T1024, B4 Hkv8 M32768 T512
+    // and B2 Hkv4 G7 M16384 T2048 (d = 128), B5 Hkv16 M15102 T433 and B3 Hkv16
+    // M3001 T333 (d = 64): within 10 % of the measured passes (e.g. G7, 8 waves
+    // in 1, 2, 4 splits: 1,060, 1,076, 973 estimated, 1,048, 1,068, 978 measured;
+    // d = 64, T433 in 1, 2, 4: 311, 231, 207 and 320, 236, 207). A rule that only
+    // filled one round took 4 waves in two splits at G7 (1,039 us and 22 of
+    // reducing) and two splits at T433 (236), seven at B1 Hkv8 d128 M2000 T300
+    // (31 us, 22 in three).
+    struct Shape4 { int waves, resident; double us[3]; };
+    static const Shape4 kD128[] = {{8, 1, {0.96, 0, 0}}, {4, 2, {0.58, 1.07, 0}}};
+    static const Shape4 kD64[] = {{4, 3, {0.39, 0.62, 0.91}}};
+    const int nshapes = s.d == 128 ? 2 : 1;
     long long nrt = 0;
-    int ns = 1;
-    p.main_waves = s.d == 128 && main_grid(8, nrt, ns) ? 8 : 4;
-    if (p.main_waves == 4) main_grid(4, nrt, ns);
+    int ns = 0;
+    double best = 0;
+    for (int v = 0; v < nshapes; ++v) {
+      const Shape4& b = s.d == 128 ? kD128[v] : kD64[v];
+      const long long rows_w = (long long)b.waves * mfma_rows_per_wave();
+      const long long nrt_v = ((long long)R + rows_w - 1) / rows_w, nb = nrt_v * (long long)BH;
+      for (int n = 1; n <= 8 && (n == 1 || n <= ntiles / 8); ++n) {
+        const long long blocks = nb * n, round = cus * b.resident;
+        const long long full = blocks / round, left = (blocks % round + cus - 1) / cus;
+        const double tiles = (double)((ntiles + n - 1) / n);
+        double us = tiles * (full * b.us[b.resident - 1] + (left ? b.us[left - 1] : 0.0)) +
+                    8.0 * (double)(full + (left != 0));
+        if (n > 1) us += 2.0 + (double)n * (double)BH * (double)R * s.d * 4.0 / 3.0e6;
+        // a clear gain is asked of more splits (their partials take memory)
+        if (ns == 0 || us < 0.97 * best) {
+          best = us;
+          ns = n;
+          nrt = nrt_v;
+          p.main_waves = b.waves;
+        }
+      }
+    }
     p.nsplit = ns;
-    // the lse pass: a round of 4-wave blocks (1,024 on 256 CUs), or of
+    // The lse pass: one round of 4-wave blocks (1,024 on 256 CUs), or of
     // 8-wave blocks where those fill whole rounds (long cache: the pass 580
-    // against 610 us; more splits than one round's worth cost the main pass
-    // as much in statistics reads)
+    // against 610 us). A grid that would be one to three partly filled rounds
+    // is cut into at least three (G7 above: 647 us at 1.75 rounds, 618 at 3.5).
     auto lse_grid = [&](int waves, int target, int& ns_w) {
       const long long rows_w = (long long)waves * mfma_rows_per_wave();
       const long long nb = (((long long)R + rows_w - 1) / rows_w) * (long long)BH;
-      ns_w = pick(nb, target, 16);
+      ns_w = pick(nb, target, kMaxLseSplit);
+      if (nb * ns_w % target != 0 && nb * ns_w > target && nb * ns_w < 3 * target &&
+          ntiles * nb >= 96ll * target)
+        ns_w = pick(nb, 3 * target, kMaxLseSplit);
       return nb * ns_w % (cus * (16 / waves)) == 0;
     };
     int nl = 1;
@@ -259,7 +288,9 @@ Plan make_plan(const Shape& s, int dtype, size_t max_bytes) {
   if (path == 2 && !decode) path = 1;
   const Plan p = path_plan(s, path);
   // (the decode kernels' stored logits are the larger part of their scratch)
-  return p.bytes <= max_bytes || path != 2 ? p : path_plan(s, 1);
+  if (p.bytes <= max_bytes || path == 0) return p;
+  const Plan p1 = path == 1 ? p : path_plan(s, 1);
+  return p1.bytes <= max_bytes ? p1 : path_plan(s, 1, true);
 }
 
 namespace {

@@ -121,6 +121,7 @@ struct Plan {
 };
 // The plan of the least time whose workspace fits max_bytes, or the smallest.
 Plan make_plan(const Shape& s, int dtype, size_t max_bytes = SIZE_MAX);
+constexpr int kMaxLseSplit = 16;  // key-range splits of the MFMA lse pass, at most
 int mfma_rows_per_wave();        // packed rows per wave of the MFMA kernels
 int decode_max_split();      // largest split-block count per head of the decode kernels
 bool decode_supports(int d, int G);   // (d, G) pairs the decode kernels handle

@@ -713,6 +713,42 @@ __device__ __forceinline__ void main_loop(int ta, int tb, int t0, int t1, MainSt
   }
 }
 
+// lambda (log2 units) of the wave's rows from the lse pass's partials of up to
+// kMaxLseSplit splits: the four lanes holding a row take every fourth split
+// each, all their loads in flight at once, and merge. (One lane reading the
+// splits in turn, twice, waited a memory latency for each: the main pass of
+// B2 Hkv8 G4 d128 M8192 T37 took 36, 42 and 54 us after 8, 16 and 32 splits.)
+// A row that sees no key (cache mode only) has no softmax, a row past R does
+// not exist: lambda +inf, every probability is 0.
+template <int NQB>
+__device__ __forceinline__ void merge_stats(float (&lam)[NQB], const float2* stats, int nsplit,
+                                            int BH, size_t bh, int R, int wrow0, int lane) {
+  constexpr int N = kMaxLseSplit / 4;
+  float2 st[NQB][N];
+#pragma unroll
+  for (int qb = 0; qb < NQB; ++qb)
+#pragma unroll
+    for (int k = 0; k < N; ++k) {
+      const int r = wrow0 + qb * 16 + (lane & 15), s = 4 * k + (lane >> 4);
+      st[qb][k] = r < R && s < nsplit ? stats[((size_t)s * BH + bh) * R + r]
+                                      : make_float2(-INFINITY, 0.f);
+    }
+#pragma unroll
+  for (int qb = 0; qb < NQB; ++qb) {
+    float mx = -INFINITY, L = 0.f;
+#pragma unroll
+    for (int k = 0; k < N; ++k) mx = fmaxf(mx, st[qb][k].x);
+    mx = fmaxf(mx, __shfl_xor(mx, 16, 64));
+    mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
+#pragma unroll
+    for (int k = 0; k < N; ++k)
+      if (st[qb][k].y > 0.f) L += st[qb][k].y * __builtin_amdgcn_exp2f(st[qb][k].x - mx);
+    L += __shfl_xor(L, 16, 64);
+    L += __shfl_xor(L, 32, 64);
+    lam[qb] = L > 0.f ? mx + __log2f(L) : INFINITY;
+  }
+}
+
 template <int D, int NW, int NQB, bool CACHE>
 __global__ __launch_bounds__(NW * 64) void main_pass(Geo g, int Hq, int Hkv, int nsplit,
                                                      int nsplit_lse, float c_log2,
@@ -747,25 +783,11 @@ __global__ __launch_bounds__(NW * 64) void main_pass(Geo g, int Hq, int Hkv, int
   load_q<D, NQB>(qf, g, b, h, Hq, wrow0, lane);
   int qi[NQB];
   float lam[NQB];
+  merge_stats<NQB>(lam, stats, nsplit_lse, BH, bh, g.R, wrow0, lane);
 #pragma unroll
   for (int qb = 0; qb < NQB; ++qb) {
     const int r = wrow0 + qb * 16 + (lane & 15);
     qi[qb] = r / g.G;
-    if (r < g.R) {
-      float mx = -INFINITY;
-      for (int s = 0; s < nsplit_lse; ++s)
-        mx = fmaxf(mx, stats[((size_t)s * BH + bh) * g.R + r].x);
-      float L = 0.f;
-      for (int s = 0; s < nsplit_lse; ++s) {
-        const float2 st = stats[((size_t)s * BH + bh) * g.R + r];
-        if (st.y > 0.f) L += st.y * __builtin_amdgcn_exp2f(st.x - mx);
-      }
-      // a row that sees no key (cache mode only) has no softmax: every
-      // probability is 0 and its lse is -inf
-      lam[qb] = L > 0.f ? mx + __log2f(L) : INFINITY;
-    } else {
-      lam[qb] = INFINITY;   // padding rows: every probability is 0
-    }
     if (sp == 0 && lane < 16 && r < g.R) {
       const int i = r / g.G, gg = r % g.G;
       lse_out[(size_t)(b * Hq + h * g.G + gg) * g.T + i] =
