@@ -11,14 +11,14 @@
 //                 held in registers, then dV^T += dO^T P and dK^T += Q^T dS
 //
 // Rows passes: a wave owns 32 packed rows (their Q and dO are B operands in
-// registers); the block's four waves share 32-key K/V tiles in LDS; the
+// registers); the block's waves share 64-key K/V tiles in LDS; the
 // transposed K operand of the dQ product comes from ds_read_b64_tr_b16.
-// Keys pass: a wave owns 16 keys (H2O_BWD_NKB blocks of 16; 16 keep the
-// wave at 200 registers, two waves per SIMD) and the waves share 32-row
-// Q/dO tiles. Its S and dP are computed in the key-per-lane orientation, so
-// P and dS leave the accumulators already laid out as the B operands of the
-// dV and dK products (two 16-row blocks per operand), and the transposed dO
-// and Q operands again come from transposing LDS reads.
+// Keys pass: two waves own 32 keys, one for S, P and dV, one for dP, dS and dK,
+// and all waves of a block share 32-row Q/dO tiles. S and dP are computed in
+// the key-per-lane orientation, so P and dS leave the accumulators already
+// laid out as the B operands of the dV and dK products (two 16-row blocks per
+// operand), and the transposed dO and Q operands again come from transposing
+// LDS reads.
 // When the rows passes would have too few blocks to fill the CUs they split
 // the key range: D partials are summed in split order (the dq pass's first
 // split leaves the sum for the keys pass), dq partials are float32 and
@@ -40,12 +40,13 @@ using namespace mfma;
 
 constexpr int kW = 4;          // waves per block
 constexpr int kNT = 64 * kW;   // threads per block
-constexpr int kTile = 32;      // keys (rows passes) or packed rows (keys pass) per LDS tile
+// Keys (rows passes) or packed rows (keys pass) per LDS tile, taken 32 at a
+// time between two barriers. Against tiles of 32, at B1 Hkv8 G4 d128 M8192 T1024
+// and at GQA 7:1 (B2 Hkv4 M16384 T2048): D pass 168 -> 159 and 1,302 -> 1,222 us,
+// keys pass 408 -> 397 and 2,464 -> 2,395, dq pass unchanged.
+constexpr int kTile = 64;
 constexpr int kPad = 16;       // bf16 past d per LDS row (pitch 288 B at d = 128)
 constexpr int kRB = kW * 32;   // packed rows per block of the rows passes (32 per wave)
-#ifndef H2O_BWD_NKB   // key blocks of 16 per wave in the keys pass
-#define H2O_BWD_NKB 1
-#endif
 
 template <int D>
 __host__ __device__ constexpr int pitch() { return D + kPad; }
@@ -140,70 +141,141 @@ __device__ __forceinline__ void store4(bf16_t* p, const f32x4& v, float mul) {
   *reinterpret_cast<u16x4*>(p) = r;
 }
 
-// 16-byte chunk e of a 32-row tile for this thread of NT: row (tid + e*NT) /
+// 16-byte chunk e of a tile for this thread of NT: row (tid + e*NT) /
 // (D/8), part (tid + e*NT) % (D/8).
-template <int D, int NT = kNT>
-constexpr int tile_chunks() { return kTile * (D / 8) / NT; }
+template <int D, int NT = kNT, int ROWS = kTile>
+constexpr int tile_chunks() { return ROWS * (D / 8) / NT; }
 
-// Keys [j0, j0 + 32) of head bh into registers (zero past the keys); in
-// cache mode threads 0..31 also fetch the keys' token positions (turned into
-// rel only when stored, so that no wait for the loads happens here). The
-// four bases come in as values so that the cache/chunk choice stays a
-// register select.
-template <int D, bool CACHE, int NT = kNT>
-__device__ __forceinline__ void load_key_tile(u32x4 (&kr)[(tile_chunks<D, NT>())],
-                                              u32x4 (&vr)[(tile_chunks<D, NT>())], int& relr,
-                                              const bf16_t* kc, const bf16_t* kn,
-                                              const bf16_t* vc, const bf16_t* vn, const BArgs& a,
-                                              size_t bh, int j0) {
-  constexpr int CH = D / 8;
-  const int tid = threadIdx.x;
-#pragma unroll
-  for (int e = 0; e < tile_chunks<D, NT>(); ++e) {
-    const int c = tid + e * NT, j = j0 + c / CH, part = c % CH;
-    const bool ok = j < a.Nk;
-    const int jj = ok ? j : 0;
-    kr[e] = load16(key_ptr<D>(kc, kn, a.M, a.T, bh, jj) + part * 8, ok);
-    vr[e] = load16(key_ptr<D>(vc, vn, a.M, a.T, bh, jj) + part * 8, ok);
-  }
-  if (CACHE && tid < kTile) relr = key_tp(a, bh, j0 + tid);
+__device__ __forceinline__ u32x4 buf16(__amdgpu_buffer_rsrc_t rs, uint32_t off) {
+  return __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(rs, (int)off, 0, 0));
 }
+constexpr uint32_t kNoRow = 0xFFFFFFF0u;   // past every buffer: reads as zero
 
-// Packed rows [r0, r0 + 32) of head (b, h): q and dout into registers, and in
-// threads 0..31 the row's lse (raw, converted when stored), D and chunk
-// position.
-template <int D, int NT = kNT>
-__device__ __forceinline__ void load_row_tile(u32x4 (&qr)[(tile_chunks<D, NT>())],
-                                              u32x4 (&orr)[(tile_chunks<D, NT>())], float& lamr,
-                                              float& dotr, int& iposr, const BArgs& a, int b,
-                                              int h, size_t bh, int r0) {
-  constexpr int CH = D / 8;
-  const int tid = threadIdx.x;
+// Keys and values of one head, tile by tile, through buffer resources over its
+// cache rows and its chunk rows: a thread's chunk is a constant byte offset
+// from the tile's first row, rows past the keys read as zero. (64-bit addresses
+// and a cache-or-chunk choice for every chunk took as many VALU instructions as
+// the passes' own arithmetic, and so did the row tiles' divisions by G: keys
+// pass 460 -> 410 us, dq 228 -> 215, D 178 -> 171 at B1 Hkv8 G4 d128 M8192 T1024.)
+template <int D, bool CACHE, int NT, int KEYS>
+struct KeyTiles {
+  static constexpr int NL = tile_chunks<D, NT, KEYS>();
+  __amdgpu_buffer_rsrc_t kc, vc, kn, vn;
+  const int32_t* tp;   // cache mode: the head's token positions
+  __device__ __forceinline__ KeyTiles(const BArgs& a, size_t bh) {
+    const uint32_t cb = (uint32_t)a.M * (uint32_t)(D * 2);
+    const uint32_t nb = CACHE ? 0u : (uint32_t)a.T * (uint32_t)(D * 2);
+    kc = buffer_rsrc(a.kc + bh * (size_t)a.M * D, cb);
+    vc = buffer_rsrc(a.vc + bh * (size_t)a.M * D, cb);
+    kn = buffer_rsrc(CACHE ? a.kc : a.kn + bh * (size_t)a.T * D, nb);
+    vn = buffer_rsrc(CACHE ? a.vc : a.vn + bh * (size_t)a.T * D, nb);
+    tp = CACHE ? a.tp + bh * (size_t)a.M : nullptr;
+  }
+  // Keys [j0, j0 + KEYS) into registers; in cache mode threads 0..KEYS-1 also fetch
+  // the keys' token positions (turned into rel only when stored, so that no
+  // wait for the loads happens here).
+  __device__ __forceinline__ void load(u32x4 (&kr)[NL], u32x4 (&vr)[NL], int& relr, int M,
+                                       int j0) const {
+    constexpr int CH = D / 8;
+    const int tid = threadIdx.x;
+    if (CACHE || j0 + KEYS <= M) {          // uniform
+      const uint32_t base = (uint32_t)j0 * (uint32_t)(D * 2) + 16u * tid;
 #pragma unroll
-  for (int e = 0; e < tile_chunks<D, NT>(); ++e) {
-    const int c = tid + e * NT, r = r0 + c / CH, part = c % CH;
-    const bool ok = r < a.R;
-    const size_t off = (ok ? row_off(a, b, h, r) : 0) * D + part * 8;
-    qr[e] = load16(a.q + off, ok);
-    orr[e] = load16(a.dout + off, ok);
+      for (int e = 0; e < NL; ++e) {
+        kr[e] = buf16(kc, base + 16u * e * NT);
+        vr[e] = buf16(vc, base + 16u * e * NT);
+      }
+    } else if (j0 >= M) {
+      const uint32_t base = (uint32_t)(j0 - M) * (uint32_t)(D * 2) + 16u * tid;
+#pragma unroll
+      for (int e = 0; e < NL; ++e) {
+        kr[e] = buf16(kn, base + 16u * e * NT);
+        vr[e] = buf16(vn, base + 16u * e * NT);
+      }
+    } else {   // the tile across M: each chunk from its own side, the other reads zero
+#pragma unroll
+      for (int e = 0; e < NL; ++e) {
+        const int c = tid + e * NT, j = j0 + c / CH;
+        const uint32_t part = 16u * (c % CH);
+        const uint32_t oc = j < M ? (uint32_t)j * (uint32_t)(D * 2) + part : kNoRow;
+        const uint32_t on = j < M ? kNoRow : (uint32_t)(j - M) * (uint32_t)(D * 2) + part;
+        kr[e] = buf16(kc, oc) | buf16(kn, on);
+        vr[e] = buf16(vc, oc) | buf16(vn, on);
+      }
+    }
+    if (CACHE && tid < KEYS) relr = j0 + tid < M ? tp[j0 + tid] : 0;
   }
-  if (tid < kTile) {
-    const int r = r0 + tid;
-    const bool ok = r < a.R;
-    lamr = ok ? a.lse[row_off(a, b, h, r)] : -INFINITY;
-    dotr = ok ? a.dfin[bh * a.R + r] : 0.f;
-    iposr = ok ? r / a.G : a.T;
-  }
-}
+};
 
-// Registers of a 32-row tile into two LDS tiles of pitch D + kPad.
-template <int D, int NT = kNT>
-__device__ __forceinline__ void store_tile(bf16_t* A, bf16_t* B,
-                                           const u32x4 (&ra)[(tile_chunks<D, NT>())],
-                                           const u32x4 (&rb)[(tile_chunks<D, NT>())]) {
+// Packed row r of a KV head as (chunk position i, query head g of its group),
+// advanced by the same count every tile: no division in the loop.
+struct RowPos {
+  int i, g;
+  __device__ __forceinline__ void set(int r, int G) {
+    i = r / G;
+    g = r % G;
+  }
+  __device__ __forceinline__ void advance(int G, int ni, int ng) {
+    i += ni;
+    g += ng;
+    if (g >= G) { g -= G; ++i; }
+  }
+};
+
+// Query rows and their output gradients, tile by tile (rows past R read as
+// zero), and in threads 0..ROWS-1 the row's lse (raw, converted when stored), D
+// and chunk position.
+template <int D, int NT, int ROWS>
+struct RowTiles {
+  static constexpr int NL = tile_chunks<D, NT, ROWS>(), CH = D / 8;
+  __amdgpu_buffer_rsrc_t q, dout;   // the G heads of the group, [G][T][D]
+  const float *lse, *dot;
+  RowPos pos[NL], mine;
+  int ni, ng;
+  __device__ __forceinline__ RowTiles(const BArgs& a, int b, int h, size_t bh, int r0) {
+    const size_t row = (size_t)(b * a.Hq + h * a.G) * a.T;
+    const uint32_t bytes = (uint32_t)a.R * (uint32_t)(D * 2);
+    q = buffer_rsrc(a.q + row * D, bytes);
+    dout = buffer_rsrc(a.dout + row * D, bytes);
+    lse = a.lse + row;
+    dot = a.dfin + bh * a.R;
+#pragma unroll
+    for (int e = 0; e < NL; ++e) pos[e].set(r0 + ((int)threadIdx.x + e * NT) / CH, a.G);
+    mine.set(r0 + (int)(threadIdx.x & (ROWS - 1)), a.G);
+    ni = ROWS / a.G;
+    ng = ROWS % a.G;
+  }
+  // The tile of rows [r0, r0 + ROWS): the tiles are taken in order.
+  __device__ __forceinline__ void load(u32x4 (&qr)[NL], u32x4 (&orr)[NL], float& lamr,
+                                       float& dotr, int& iposr, const BArgs& a, int r0) {
+    const int tid = threadIdx.x;
+#pragma unroll
+    for (int e = 0; e < NL; ++e) {
+      const int c = tid + e * NT;
+      const uint32_t row = (uint32_t)(pos[e].g * a.T + pos[e].i);
+      const uint32_t o = row * (uint32_t)(D * 2) + 16u * (c % CH);
+      const uint32_t off = r0 + c / CH < a.R ? o : kNoRow;
+      qr[e] = buf16(q, off);
+      orr[e] = buf16(dout, off);
+      pos[e].advance(a.G, ni, ng);
+    }
+    if (tid < ROWS) {
+      const bool ok = r0 + tid < a.R;
+      lamr = ok ? lse[mine.g * a.T + mine.i] : -INFINITY;
+      dotr = ok ? dot[r0 + tid] : 0.f;
+      iposr = ok ? mine.i : a.T;
+    }
+    mine.advance(a.G, ni, ng);
+  }
+};
+
+// Registers of a tile into two LDS tiles of pitch D + kPad.
+template <int D, int NT = kNT, int N>
+__device__ __forceinline__ void store_tile(bf16_t* A, bf16_t* B, const u32x4 (&ra)[N],
+                                           const u32x4 (&rb)[N]) {
   constexpr int CH = D / 8, P = pitch<D>();
 #pragma unroll
-  for (int e = 0; e < tile_chunks<D, NT>(); ++e) {
+  for (int e = 0; e < N; ++e) {
     const int c = threadIdx.x + e * NT, row = c / CH, part = c % CH;
     *reinterpret_cast<u32x4*>(&A[row * P + part * 8]) = ra[e];
     *reinterpret_cast<u32x4*>(&B[row * P + part * 8]) = rb[e];
@@ -215,11 +287,11 @@ __device__ __forceinline__ void store_tile(bf16_t* A, bf16_t* B,
 // grid fills whole rounds of the CUs).
 template <int D, bool DQ, bool CACHE, int NW = kW>
 __global__ __launch_bounds__(NW * 64) void bwd_rows(BArgs a) {
-  constexpr int NT = NW * 64, RB = NW * 32;
-  constexpr int P = pitch<D>(), KS = D / 32, NL = tile_chunks<D, NT>();
-  __shared__ __attribute__((aligned(16))) bf16_t Ks[2][kTile * P];
-  __shared__ __attribute__((aligned(16))) bf16_t Vs[2][kTile * P];
-  __shared__ __attribute__((aligned(16))) int rel_s[2][kTile];
+  constexpr int NT = NW * 64, RB = NW * 32, KEYS = kTile;
+  constexpr int P = pitch<D>(), KS = D / 32, NL = tile_chunks<D, NT, KEYS>();
+  __shared__ __attribute__((aligned(16))) bf16_t Ks[2][KEYS * P];
+  __shared__ __attribute__((aligned(16))) bf16_t Vs[2][KEYS * P];
+  __shared__ __attribute__((aligned(16))) int rel_s[2][KEYS];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int g4 = lane >> 4, l16 = lane & 15;
   int xb, bhi;
@@ -261,7 +333,7 @@ __global__ __launch_bounds__(NW * 64) void bwd_rows(BArgs a) {
   const int kv_end =
       CACHE ? a.M : kv_end_for_rows(min(rblk + RB, a.R), a.G, a.T, a.M, a.Nk - a.M);
   // this split's share of the block's key tiles (possibly none)
-  const int ntiles_all = (kv_end + kTile - 1) / kTile;
+  const int ntiles_all = (kv_end + KEYS - 1) / KEYS;
   const int tb = (int)((long long)sp * ntiles_all / a.ns);
   const int te = (int)((long long)(sp + 1) * ntiles_all / a.ns);
 
@@ -275,66 +347,68 @@ __global__ __launch_bounds__(NW * 64) void bwd_rows(BArgs a) {
     for (int qb = 0; qb < 2; ++qb) dqacc[db][qb] = f32x4{0.f, 0.f, 0.f, 0.f};
   float dsum[2] = {0.f, 0.f};
 
-  if (tb < te)
-    load_key_tile<D, CACHE, NT>(kr, vr, relr, a.kc, a.kn, a.vc, a.vn, a, bh, tb * kTile);
+  const KeyTiles<D, CACHE, NT, KEYS> kt(a, bh);
+  if (tb < te) kt.load(kr, vr, relr, a.M, tb * KEYS);
   for (int t = tb; t < te; ++t) {
-    const int buf = (t - tb) & 1, j0 = t * kTile;
+    const int buf = (t - tb) & 1;
     store_tile<D, NT>(Ks[buf], Vs[buf], kr, vr);
-    if (CACHE && tid < kTile) rel_s[buf][tid] = key_rel_of(a, j0 + tid, relr);
+    if (CACHE && tid < KEYS) rel_s[buf][tid] = key_rel_of(a, t * KEYS + tid, relr);
     __syncthreads();
-    if (t + 1 < te)
-      load_key_tile<D, CACHE, NT>(kr, vr, relr, a.kc, a.kn, a.vc, a.vn, a, bh,
-                                  (t + 1) * kTile);
+    if (t + 1 < te) kt.load(kr, vr, relr, a.M, (t + 1) * KEYS);
     if (!live) continue;
-    const bf16_t* Kt = Ks[buf];
-    const bf16_t* Vt = Vs[buf];
-    f32x4 sacc[2][2], pacc[2][2];   // [kb][qb]: keys 16kb + 4g4 + u, query l16
 #pragma unroll
-    for (int kb = 0; kb < 2; ++kb)
+    for (int k0 = 0; k0 < KEYS; k0 += 32) {
+      const int j0 = t * KEYS + k0;
+      const bf16_t* Kt = Ks[buf] + k0 * P;
+      const bf16_t* Vt = Vs[buf] + k0 * P;
+      f32x4 sacc[2][2], pacc[2][2];   // [kb][qb]: keys 16kb + 4g4 + u, query l16
 #pragma unroll
-      for (int qb = 0; qb < 2; ++qb) sacc[kb][qb] = pacc[kb][qb] = f32x4{0.f, 0.f, 0.f, 0.f};
+      for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
-    for (int s = 0; s < KS; ++s)
+        for (int qb = 0; qb < 2; ++qb) sacc[kb][qb] = pacc[kb][qb] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-      for (int kb = 0; kb < 2; ++kb) {
-        const bf16x8 ak = row_operand(Kt, P, 16 * kb + l16, 32 * s, lane);
-        const bf16x8 av = row_operand(Vt, P, 16 * kb + l16, 32 * s, lane);
+      for (int s = 0; s < KS; ++s)
 #pragma unroll
-        for (int qb = 0; qb < 2; ++qb) {
-          sacc[kb][qb] = mma(ak, qf[qb][s], sacc[kb][qb]);
-          pacc[kb][qb] = mma(av, df[qb][s], pacc[kb][qb]);
+        for (int kb = 0; kb < 2; ++kb) {
+          const bf16x8 ak = row_operand(Kt, P, 16 * kb + l16, 32 * s, lane);
+          const bf16x8 av = row_operand(Vt, P, 16 * kb + l16, 32 * s, lane);
+#pragma unroll
+          for (int qb = 0; qb < 2; ++qb) {
+            sacc[kb][qb] = mma(ak, qf[qb][s], sacc[kb][qb]);
+            pacc[kb][qb] = mma(av, df[qb][s], pacc[kb][qb]);
+          }
         }
-      }
-    // wave-uniform: every key of the tile visible to every row of the wave
-    const bool full = !CACHE && j0 + kTile - 1 - a.M <= imin;
-    int rel[2][4];
+      // wave-uniform: every key of the tile visible to every row of the wave
+      const bool full = !CACHE && j0 + 31 - a.M <= imin;
+      int rel[2][4];
 #pragma unroll
-    for (int kb = 0; kb < 2; ++kb)
-#pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        const int jl = 16 * kb + 4 * g4 + u, j = j0 + jl;
-        rel[kb][u] = CACHE ? rel_s[buf][jl] : (j < a.M ? -1 : j - a.M);
-      }
-#pragma unroll
-    for (int kb = 0; kb < 2; ++kb)
-#pragma unroll
-      for (int qb = 0; qb < 2; ++qb)
+      for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
-          float p = __builtin_amdgcn_exp2f(fmaf(sacc[kb][qb][u], a.c, -lam[qb]));
-          if (!full && rel[kb][u] > ipos[qb]) p = 0.f;
-          if (DQ) sacc[kb][qb][u] = p * (pacc[kb][qb][u] - dr[qb]);
-          else dsum[qb] = fmaf(p, pacc[kb][qb][u], dsum[qb]);
+          const int jl = 16 * kb + 4 * g4 + u, j = j0 + jl;
+          rel[kb][u] = CACHE ? rel_s[buf][k0 + jl] : (j < a.M ? -1 : j - a.M);
         }
-    if (DQ) {
-      bf16x8 dsop[2];
 #pragma unroll
-      for (int qb = 0; qb < 2; ++qb) dsop[qb] = pack_pair(sacc[0][qb], sacc[1][qb]);
+      for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
-      for (int db = 0; db < D / 16; ++db) {
-        const bf16x8 ak = tr_operand(Kt, P, db, lane);
+        for (int qb = 0; qb < 2; ++qb)
 #pragma unroll
-        for (int qb = 0; qb < 2; ++qb) dqacc[db][qb] = mma(ak, dsop[qb], dqacc[db][qb]);
+          for (int u = 0; u < 4; ++u) {
+            float p = __builtin_amdgcn_exp2f(fmaf(sacc[kb][qb][u], a.c, -lam[qb]));
+            if (!full && rel[kb][u] > ipos[qb]) p = 0.f;
+            if (DQ) sacc[kb][qb][u] = p * (pacc[kb][qb][u] - dr[qb]);
+            else dsum[qb] = fmaf(p, pacc[kb][qb][u], dsum[qb]);
+          }
+      if (DQ) {
+        bf16x8 dsop[2];
+#pragma unroll
+        for (int qb = 0; qb < 2; ++qb) dsop[qb] = pack_pair(sacc[0][qb], sacc[1][qb]);
+#pragma unroll
+        for (int db = 0; db < D / 16; ++db) {
+          const bf16x8 ak = tr_operand(Kt, P, db, lane);
+#pragma unroll
+          for (int qb = 0; qb < 2; ++qb) dqacc[db][qb] = mma(ak, dsop[qb], dqacc[db][qb]);
+        }
       }
     }
   }
@@ -367,13 +441,13 @@ __global__ __launch_bounds__(NW * 64) void bwd_rows(BArgs a) {
 // A wave owns NKB*16 keys (NKB key blocks of 16).
 template <int D, int NKB, bool CACHE, int NW = kW>
 __global__ __launch_bounds__(NW * 64) void bwd_keys(BArgs a) {
-  constexpr int NT = NW * 64;
-  constexpr int P = pitch<D>(), KS = D / 32, NL = tile_chunks<D, NT>();
-  __shared__ __attribute__((aligned(16))) bf16_t Qs[2][kTile * P];
-  __shared__ __attribute__((aligned(16))) bf16_t Os[2][kTile * P];
-  __shared__ __attribute__((aligned(16))) float lam_s[2][kTile];
-  __shared__ __attribute__((aligned(16))) float dot_s[2][kTile];
-  __shared__ __attribute__((aligned(16))) int ipos_s[2][kTile];
+  constexpr int NT = NW * 64, ROWS = kTile;
+  constexpr int P = pitch<D>(), KS = D / 32, NL = tile_chunks<D, NT, ROWS>();
+  __shared__ __attribute__((aligned(16))) bf16_t Qs[2][ROWS * P];
+  __shared__ __attribute__((aligned(16))) bf16_t Os[2][ROWS * P];
+  __shared__ __attribute__((aligned(16))) float lam_s[2][ROWS];
+  __shared__ __attribute__((aligned(16))) float dot_s[2][ROWS];
+  __shared__ __attribute__((aligned(16))) int ipos_s[2][ROWS];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int g4 = lane >> 4, l16 = lane & 15;
   int xb, bhi;
@@ -411,8 +485,8 @@ __global__ __launch_bounds__(NW * 64) void bwd_keys(BArgs a) {
   // the block's first row tile that may see one of its keys (chunk mode: the
   // first chunk key of the block; cache mode: row 0)
   const int rel_first = CACHE ? -1 : (kblk < a.M ? -1 : kblk - a.M);
-  const int t0 = (rel_first < 0 ? 0 : rel_first * a.G) / kTile;
-  const int t1 = (a.R + kTile - 1) / kTile;
+  const int t0 = (rel_first < 0 ? 0 : rel_first * a.G) / ROWS;
+  const int t1 = (a.R + ROWS - 1) / ROWS;
 
   u32x4 qr[NL], orr[NL];
   float lamr = 0.f, dotr = 0.f;
@@ -424,70 +498,73 @@ __global__ __launch_bounds__(NW * 64) void bwd_keys(BArgs a) {
 #pragma unroll
     for (int kb = 0; kb < NKB; ++kb) dkacc[db][kb] = dvacc[db][kb] = f32x4{0.f, 0.f, 0.f, 0.f};
 
-  if (t0 < t1) load_row_tile<D, NT>(qr, orr, lamr, dotr, iposr, a, b, h, bh, t0 * kTile);
+  RowTiles<D, NT, ROWS> rt(a, b, h, bh, t0 * ROWS);
+  if (t0 < t1) rt.load(qr, orr, lamr, dotr, iposr, a, t0 * ROWS);
   for (int t = t0; t < t1; ++t) {
     const int buf = (t - t0) & 1;
     store_tile<D, NT>(Qs[buf], Os[buf], qr, orr);
-    if (tid < kTile) {
+    if (tid < ROWS) {
       lam_s[buf][tid] = lambda_of(lamr);
       dot_s[buf][tid] = dotr;
       ipos_s[buf][tid] = iposr;
     }
     __syncthreads();
-    if (t + 1 < t1)
-      load_row_tile<D, NT>(qr, orr, lamr, dotr, iposr, a, b, h, bh, (t + 1) * kTile);
+    if (t + 1 < t1) rt.load(qr, orr, lamr, dotr, iposr, a, (t + 1) * ROWS);
     if (!live) continue;
-    const bf16_t* Qt = Qs[buf];
-    const bf16_t* Ot = Os[buf];
-    f32x4 sacc[2][NKB], pacc[2][NKB];   // [rb][kb]: rows 16rb + 4g4 + u, key 16kb + l16
 #pragma unroll
-    for (int rb = 0; rb < 2; ++rb)
+    for (int r0 = 0; r0 < ROWS; r0 += 32) {
+      const bf16_t* Qt = Qs[buf] + r0 * P;
+      const bf16_t* Ot = Os[buf] + r0 * P;
+      f32x4 sacc[2][NKB], pacc[2][NKB];   // [rb][kb]: rows 16rb + 4g4 + u, key 16kb + l16
 #pragma unroll
-      for (int kb = 0; kb < NKB; ++kb) sacc[rb][kb] = pacc[rb][kb] = f32x4{0.f, 0.f, 0.f, 0.f};
+      for (int rb = 0; rb < 2; ++rb)
 #pragma unroll
-    for (int s = 0; s < KS; ++s)
+        for (int kb = 0; kb < NKB; ++kb) sacc[rb][kb] = pacc[rb][kb] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int s = 0; s < KS; ++s)
+#pragma unroll
+        for (int rb = 0; rb < 2; ++rb) {
+          const bf16x8 aq = row_operand(Qt, P, 16 * rb + l16, 32 * s, lane);
+          const bf16x8 ad = row_operand(Ot, P, 16 * rb + l16, 32 * s, lane);
+#pragma unroll
+          for (int kb = 0; kb < NKB; ++kb) {
+            sacc[rb][kb] = mma(aq, kf[kb][s], sacc[rb][kb]);
+            pacc[rb][kb] = mma(ad, vf[kb][s], pacc[rb][kb]);
+          }
+        }
+      const bool full = relmax <= (t * ROWS) / a.G;
 #pragma unroll
       for (int rb = 0; rb < 2; ++rb) {
-        const bf16x8 aq = row_operand(Qt, P, 16 * rb + l16, 32 * s, lane);
-        const bf16x8 ad = row_operand(Ot, P, 16 * rb + l16, 32 * s, lane);
+        const f32x4 lam4 = *reinterpret_cast<const f32x4*>(&lam_s[buf][r0 + 16 * rb + 4 * g4]);
+        const f32x4 dot4 = *reinterpret_cast<const f32x4*>(&dot_s[buf][r0 + 16 * rb + 4 * g4]);
+        int ip4[4];
 #pragma unroll
-        for (int kb = 0; kb < NKB; ++kb) {
-          sacc[rb][kb] = mma(aq, kf[kb][s], sacc[rb][kb]);
-          pacc[rb][kb] = mma(ad, vf[kb][s], pacc[rb][kb]);
-        }
+        for (int u = 0; u < 4; ++u) ip4[u] = ipos_s[buf][r0 + 16 * rb + 4 * g4 + u];
+#pragma unroll
+        for (int kb = 0; kb < NKB; ++kb)
+#pragma unroll
+          for (int u = 0; u < 4; ++u) {
+            float p = __builtin_amdgcn_exp2f(fmaf(sacc[rb][kb][u], a.c, -lam4[u]));
+            if (!full && rel[kb] > ip4[u]) p = 0.f;
+            pacc[rb][kb][u] = p * (pacc[rb][kb][u] - dot4[u]);
+            sacc[rb][kb][u] = p;
+          }
       }
-    const bool full = relmax <= (t * kTile) / a.G;
-#pragma unroll
-    for (int rb = 0; rb < 2; ++rb) {
-      const f32x4 lam4 = *reinterpret_cast<const f32x4*>(&lam_s[buf][16 * rb + 4 * g4]);
-      const f32x4 dot4 = *reinterpret_cast<const f32x4*>(&dot_s[buf][16 * rb + 4 * g4]);
-      int ip4[4];
-#pragma unroll
-      for (int u = 0; u < 4; ++u) ip4[u] = ipos_s[buf][16 * rb + 4 * g4 + u];
-#pragma unroll
-      for (int kb = 0; kb < NKB; ++kb)
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-          float p = __builtin_amdgcn_exp2f(fmaf(sacc[rb][kb][u], a.c, -lam4[u]));
-          if (!full && rel[kb] > ip4[u]) p = 0.f;
-          pacc[rb][kb][u] = p * (pacc[rb][kb][u] - dot4[u]);
-          sacc[rb][kb][u] = p;
-        }
-    }
-    bf16x8 pop[NKB], dsop[NKB];
-#pragma unroll
-    for (int kb = 0; kb < NKB; ++kb) {
-      pop[kb] = pack_pair(sacc[0][kb], sacc[1][kb]);
-      dsop[kb] = pack_pair(pacc[0][kb], pacc[1][kb]);
-    }
-#pragma unroll
-    for (int db = 0; db < D / 16; ++db) {
-      const bf16x8 ao = tr_operand(Ot, P, db, lane);
-      const bf16x8 aq = tr_operand(Qt, P, db, lane);
+      bf16x8 pop[NKB], dsop[NKB];
 #pragma unroll
       for (int kb = 0; kb < NKB; ++kb) {
-        dvacc[db][kb] = mma(ao, pop[kb], dvacc[db][kb]);
-        dkacc[db][kb] = mma(aq, dsop[kb], dkacc[db][kb]);
+        pop[kb] = pack_pair(sacc[0][kb], sacc[1][kb]);
+        dsop[kb] = pack_pair(pacc[0][kb], pacc[1][kb]);
+      }
+#pragma unroll
+      for (int db = 0; db < D / 16; ++db) {
+        const bf16x8 ao = tr_operand(Ot, P, db, lane);
+        const bf16x8 aq = tr_operand(Qt, P, db, lane);
+#pragma unroll
+        for (int kb = 0; kb < NKB; ++kb) {
+          dvacc[db][kb] = mma(ao, pop[kb], dvacc[db][kb]);
+          dkacc[db][kb] = mma(aq, dsop[kb], dkacc[db][kb]);
+        }
       }
     }
   }
@@ -561,9 +638,8 @@ hipError_t run(const Shape& s, const BackwardPlan& pl, BArgs a, hipStream_t st) 
     if (e != hipSuccess) return e;
   }
   if (s.Nk() == 0) return hipSuccess;
-  constexpr int NKB = H2O_BWD_NKB;
-  const dim3 gkeys((s.Nk() + kW * 16 * NKB - 1) / (kW * 16 * NKB), BH);
-  return launch_kernel(K_BWD_DKDV, bwd_keys<D, NKB, CACHE>, gkeys, dim3(kNT), st, a);
+  const dim3 gkeys((s.Nk() + kW * 16 - 1) / (kW * 16), BH);
+  return launch_kernel(K_BWD_DKDV, bwd_keys<D, 1, CACHE>, gkeys, dim3(kNT), st, a);
 }
 
 }  // namespace
@@ -572,8 +648,8 @@ hipError_t run(const Shape& s, const BackwardPlan& pl, BArgs a, hipStream_t st) 
 #define H2O_DOT8_PER_CU 1
 #endif
 // Splits of the key range of the two rows passes, so that their grids fill
-// the CUs (the D pass runs three 4-wave blocks per CU, the dq pass two);
-// at least 8 key tiles per split. At d = 128 either pass runs 8-wave blocks
+// the CUs (two 4-wave blocks per CU, three for the D pass at d = 64);
+// at least 8 times 32 keys per split. At d = 128 either pass runs 8-wave blocks
 // (one per CU) where those fill whole rounds of the CUs.
 BackwardPlan backward_plan(const Shape& s, int dtype) {
   BackwardPlan p{1, 1, 0, 0, 4, 4};
@@ -581,14 +657,14 @@ BackwardPlan backward_plan(const Shape& s, int dtype) {
   size_t bytes = align256_size(BH * R * sizeof(float));
   if (dtype == 1 && R > 0) {
     const long long blocks = (long long)((R + kRB - 1) / kRB) * (long long)BH;
-    const long long ntiles = (s.Nk() + kTile - 1) / kTile;
+    const long long ntiles = (s.Nk() + 31) / 32;
     const long long cus = device_cus();
     auto pick = [&](long long nb, long long target) {
       long long ns = (target + nb - 1) / nb;
       ns = std::min(ns, std::max(1LL, ntiles / 8));
       return (int)std::max(1LL, std::min(ns, 8LL));
     };
-    p.ns_dot = pick(blocks, 3 * cus);
+    p.ns_dot = pick(blocks, (s.d == 64 ? 3 : 2) * cus);
     p.ns_dq = pick(blocks, 2 * cus);
     // at d = 128 the dq pass runs 8-wave blocks (256 rows, one per CU) where
     // their grid fills whole rounds: the waves sharing a SIMD then come from
@@ -600,7 +676,7 @@ BackwardPlan backward_plan(const Shape& s, int dtype) {
         p.dq_waves = 8;
         p.ns_dq = ns8;
       }
-      // the D pass likewise (three waves per SIMD fit, so one 8-wave block per CU)
+      // the D pass likewise (one 8-wave block per CU)
       const int nsd8 = pick(blocks8, H2O_DOT8_PER_CU * cus);
       if (H2O_DOT8_PER_CU > 0 && blocks8 * nsd8 % (H2O_DOT8_PER_CU * cus) == 0) {
         p.dot_waves = 8;
