@@ -58,25 +58,26 @@ int ok() {
 
 bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
 
-// Checks that a usable gfx950 device is current. Cached per device id.
+// Checks that a usable gfx950 device is current. A device's answer is kept;
+// the call for a known one is a look at the current device alone.
 int check_device() {
+  static std::atomic<int> known[64];   // 0 unknown, 1 ok, 2 bad
+  int dev = 0;
+  if (hipGetDevice(&dev) == hipSuccess && dev >= 0 && dev < 64 && known[dev].load() == 1)
+    return H2O_OK;
   int n = 0;
   if (hipGetDeviceCount(&n) != hipSuccess || n <= 0) {
     (void)hipGetLastError();
     return fail(H2O_ENODEVICE, "no HIP device visible");
   }
-  int dev = 0;
   if (hipGetDevice(&dev) != hipSuccess) return fail(H2O_ENODEVICE, "hipGetDevice failed");
-  static std::mutex mu;
-  static int known[64] = {0};   // 0 unknown, 1 ok, 2 bad
-  std::lock_guard<std::mutex> lk(mu);
-  if (dev >= 0 && dev < 64 && known[dev] == 0) {
+  if (dev >= 0 && dev < 64 && known[dev].load() == 0) {
     hipDeviceProp_t prop;
     if (hipGetDeviceProperties(&prop, dev) != hipSuccess)
       return fail(H2O_ENODEVICE, "hipGetDeviceProperties failed");
-    known[dev] = std::strncmp(prop.gcnArchName, "gfx950", 6) == 0 ? 1 : 2;
+    known[dev].store(std::strncmp(prop.gcnArchName, "gfx950", 6) == 0 ? 1 : 2);
   }
-  if (dev < 0 || dev >= 64 || known[dev] != 1)
+  if (dev < 0 || dev >= 64 || known[dev].load() != 1)
     return fail(H2O_ENODEVICE, "device %d is not a gfx950 (MI355X) GPU", dev);
   return H2O_OK;
 }

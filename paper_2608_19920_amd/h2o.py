@@ -137,8 +137,15 @@ def _dev(t: Optional[torch.Tensor], name: str):
     return t.data_ptr()
 
 
+# The current stream's handle without building a torch.cuda.Stream around it
+# (1.5 us a call), where this torch has the accessor.
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _stream(stream) -> Optional[int]:
     if stream is None:
+        if _raw_stream is not None:
+            return _raw_stream(torch.cuda.current_device())
         return torch.cuda.current_stream().cuda_stream
     return stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream)
 
@@ -180,15 +187,15 @@ def h2o_sdpa_chunk(q, k_cache, v_cache, k_new, v_new, out, lse, wsum, workspace,
                     ("v_new", v_new), ("out", out)):
         if t.dtype != q.dtype:
             raise TypeError(f"{name} dtype {t.dtype} != q dtype {q.dtype}")
-    if tuple(k_cache.shape) != (B, Hkv, M, d) or tuple(v_cache.shape) != (B, Hkv, M, d):
+    if k_cache.shape != (B, Hkv, M, d) or v_cache.shape != (B, Hkv, M, d):
         raise ValueError("cache shape mismatch")
-    if tuple(k_new.shape) != (B, Hkv, T, d) or tuple(v_new.shape) != (B, Hkv, T, d):
+    if k_new.shape != (B, Hkv, T, d) or v_new.shape != (B, Hkv, T, d):
         raise ValueError("k_new/v_new shape mismatch")
-    if tuple(out.shape) != (B, Hq, T, d):
+    if out.shape != (B, Hq, T, d):
         raise ValueError("out shape mismatch")
-    if tuple(lse.shape) != (B, Hq, T) or lse.dtype != torch.float32:
+    if lse.shape != (B, Hq, T) or lse.dtype != torch.float32:
         raise ValueError("lse must be float32 [B,Hq,T]")
-    if tuple(wsum.shape) != (B, Hkv, M + T) or wsum.dtype != torch.float32:
+    if wsum.shape != (B, Hkv, M + T) or wsum.dtype != torch.float32:
         raise ValueError("wsum must be float32 [B,Hkv,M+T]")
     if scale is None:
         scale = d ** -0.5
@@ -206,7 +213,7 @@ def h2o_accumulate_scores(scores, wsum, stream=None) -> None:
     T = wsum.shape[2] - M
     if scores.dtype != torch.float32 or wsum.dtype != torch.float32:
         raise TypeError("scores and wsum must be float32")
-    if tuple(wsum.shape[:2]) != (B, Hkv) or T < 0:
+    if wsum.shape[:2] != (B, Hkv) or T < 0:
         raise ValueError("wsum shape mismatch")
     _check(lib().h2o_accumulate_scores(_dev(scores, "scores"), _dev(wsum, "wsum"),
                                        B, Hkv, M, T, _stream(stream)))
@@ -220,17 +227,17 @@ def _evict_args(k_cache, v_cache, scores, token_pos, k_new, v_new, wsum, evict_i
     if v_cache.dtype != k_cache.dtype or k_new.dtype != k_cache.dtype or \
             v_new.dtype != k_cache.dtype:
         raise TypeError("cache and chunk tensors must share one dtype")
-    if tuple(v_cache.shape) != (B, Hkv, M, d) or tuple(k_new.shape) != (B, Hkv, T, d) or \
-            tuple(v_new.shape) != (B, Hkv, T, d):
+    if v_cache.shape != (B, Hkv, M, d) or k_new.shape != (B, Hkv, T, d) or \
+            v_new.shape != (B, Hkv, T, d):
         raise ValueError("shape mismatch")
-    if tuple(scores.shape) != (B, Hkv, M) or scores.dtype != torch.float32:
+    if scores.shape != (B, Hkv, M) or scores.dtype != torch.float32:
         raise ValueError("scores must be float32 [B,Hkv,M]")
-    if tuple(wsum.shape) != (B, Hkv, M + T) or wsum.dtype != torch.float32:
+    if wsum.shape != (B, Hkv, M + T) or wsum.dtype != torch.float32:
         raise ValueError("wsum must be float32 [B,Hkv,M+T]")
-    if evict_idx.dtype != torch.int32 or tuple(evict_idx.shape[:2]) != (B, Hkv):
+    if evict_idx.dtype != torch.int32 or evict_idx.shape[:2] != (B, Hkv):
         raise ValueError("evict_idx must be int32 [B,Hkv,k]")
     if token_pos is not None and (token_pos.dtype != torch.int32 or
-                                  tuple(token_pos.shape) != (B, Hkv, M)):
+                                  token_pos.shape != (B, Hkv, M)):
         raise ValueError("token_pos must be int32 [B,Hkv,M]")
     ptrs = (_dev(k_cache, "k_cache"), _dev(v_cache, "v_cache"), _dev(scores, "scores"),
             _dev(token_pos, "token_pos"), _dev(k_new, "k_new"), _dev(v_new, "v_new"),
@@ -270,14 +277,17 @@ def h2o_evict_insert_policy(k_cache, v_cache, scores, token_pos, k_new, v_new, w
                                          _stream(stream)))
 
 
+_STEP_PART = {"all": "h2o_chunk_step", "attend": "h2o_chunk_step_attend",
+              "evict": "h2o_chunk_step_evict"}
+
+
 def h2o_chunk_step(q, k_cache, v_cache, scores, token_pos, k_new, v_new, out, lse, wsum,
                    evict_idx, workspace, pos0: int, scale: Optional[float] = None,
                    stream=None, part: str = "all") -> None:
     """h2o_sdpa_chunk + h2o_accumulate_scores + h2o_evict_insert (k = T) in one
     call; shapes as there. ``part`` "attend" / "evict" calls one half
     (h2o_chunk_step_attend / h2o_chunk_step_evict)."""
-    fn = {"all": "h2o_chunk_step", "attend": "h2o_chunk_step_attend",
-          "evict": "h2o_chunk_step_evict"}[part]
+    fn = _STEP_PART[part]
     B, Hq, T, d = q.shape
     Hkv, M = k_cache.shape[1], k_cache.shape[2]
     dt = _dtype_code(q)
@@ -285,20 +295,20 @@ def h2o_chunk_step(q, k_cache, v_cache, scores, token_pos, k_new, v_new, out, ls
                     ("v_new", v_new), ("out", out)):
         if t.dtype != q.dtype:
             raise TypeError(f"{name} dtype {t.dtype} != q dtype {q.dtype}")
-    if tuple(k_cache.shape) != (B, Hkv, M, d) or tuple(v_cache.shape) != (B, Hkv, M, d) or \
-            tuple(k_new.shape) != (B, Hkv, T, d) or tuple(v_new.shape) != (B, Hkv, T, d) or \
-            tuple(out.shape) != (B, Hq, T, d):
+    if k_cache.shape != (B, Hkv, M, d) or v_cache.shape != (B, Hkv, M, d) or \
+            k_new.shape != (B, Hkv, T, d) or v_new.shape != (B, Hkv, T, d) or \
+            out.shape != (B, Hq, T, d):
         raise ValueError("shape mismatch")
-    if tuple(lse.shape) != (B, Hq, T) or lse.dtype != torch.float32:
+    if lse.shape != (B, Hq, T) or lse.dtype != torch.float32:
         raise ValueError("lse must be float32 [B,Hq,T]")
-    if tuple(wsum.shape) != (B, Hkv, M + T) or wsum.dtype != torch.float32:
+    if wsum.shape != (B, Hkv, M + T) or wsum.dtype != torch.float32:
         raise ValueError("wsum must be float32 [B,Hkv,M+T]")
-    if tuple(scores.shape) != (B, Hkv, M) or scores.dtype != torch.float32:
+    if scores.shape != (B, Hkv, M) or scores.dtype != torch.float32:
         raise ValueError("scores must be float32 [B,Hkv,M]")
-    if tuple(evict_idx.shape) != (B, Hkv, T) or evict_idx.dtype != torch.int32:
+    if evict_idx.shape != (B, Hkv, T) or evict_idx.dtype != torch.int32:
         raise ValueError("evict_idx must be int32 [B,Hkv,T]")
     if token_pos is not None and (token_pos.dtype != torch.int32 or
-                                  tuple(token_pos.shape) != (B, Hkv, M)):
+                                  token_pos.shape != (B, Hkv, M)):
         raise ValueError("token_pos must be int32 [B,Hkv,M]")
     if scale is None:
         scale = d ** -0.5
@@ -323,15 +333,15 @@ def _cache_args(q, k_cache, v_cache, token_pos, out, lse, wsum):
     for name, t in (("k_cache", k_cache), ("v_cache", v_cache), ("out", out)):
         if t.dtype != q.dtype:
             raise TypeError(f"{name} dtype {t.dtype} != q dtype {q.dtype}")
-    if tuple(k_cache.shape) != (B, Hkv, M, d) or tuple(v_cache.shape) != (B, Hkv, M, d) or \
-            tuple(out.shape) != (B, Hq, T, d):
+    if k_cache.shape != (B, Hkv, M, d) or v_cache.shape != (B, Hkv, M, d) or \
+            out.shape != (B, Hq, T, d):
         raise ValueError("shape mismatch")
     if token_pos is None or token_pos.dtype != torch.int32 or \
-            tuple(token_pos.shape) != (B, Hkv, M):
+            token_pos.shape != (B, Hkv, M):
         raise ValueError("token_pos must be int32 [B,Hkv,M]")
-    if tuple(lse.shape) != (B, Hq, T) or lse.dtype != torch.float32:
+    if lse.shape != (B, Hq, T) or lse.dtype != torch.float32:
         raise ValueError("lse must be float32 [B,Hq,T]")
-    if tuple(wsum.shape) != (B, Hkv, M) or wsum.dtype != torch.float32:
+    if wsum.shape != (B, Hkv, M) or wsum.dtype != torch.float32:
         raise ValueError("wsum must be float32 [B,Hkv,M]")
     return B, Hq, Hkv, T, M, d
 
@@ -363,10 +373,10 @@ def h2o_chunk_step_noalloc(q, k_cache, v_cache, scores, token_pos, k_new, v_new,
     (h2o_noalloc_scratch_bytes) serves instead; shapes as in h2o_chunk_step."""
     B, Hq, T, d = q.shape
     Hkv, M = k_cache.shape[1], k_cache.shape[2]
-    if tuple(wsum.shape) != (B, Hkv, M + T) or tuple(evict_idx.shape) != (B, Hkv, T) or \
-            tuple(scores.shape) != (B, Hkv, M) or tuple(out.shape) != (B, Hq, T, d) or \
-            tuple(k_new.shape) != (B, Hkv, T, d) or tuple(v_new.shape) != (B, Hkv, T, d) or \
-            tuple(lse.shape) != (B, Hq, T):
+    if wsum.shape != (B, Hkv, M + T) or evict_idx.shape != (B, Hkv, T) or \
+            scores.shape != (B, Hkv, M) or out.shape != (B, Hq, T, d) or \
+            k_new.shape != (B, Hkv, T, d) or v_new.shape != (B, Hkv, T, d) or \
+            lse.shape != (B, Hq, T):
         raise ValueError("shape mismatch")
     if scale is None:
         scale = d ** -0.5
@@ -386,11 +396,11 @@ def h2o_chunk_step_insert_first(q, k_cache, v_cache, scores, token_pos, k_new, v
     with the token-position mask, accumulate; wsum [B,Hkv,M]."""
     B, Hq, Hkv, T, M, d = _cache_args(q, k_cache, v_cache, token_pos, out, lse, wsum)
     if k_new.dtype != q.dtype or v_new.dtype != q.dtype or \
-            tuple(k_new.shape) != (B, Hkv, T, d) or tuple(v_new.shape) != (B, Hkv, T, d):
+            k_new.shape != (B, Hkv, T, d) or v_new.shape != (B, Hkv, T, d):
         raise ValueError("k_new/v_new must be [B,Hkv,T,d] in q's dtype")
-    if tuple(scores.shape) != (B, Hkv, M) or scores.dtype != torch.float32:
+    if scores.shape != (B, Hkv, M) or scores.dtype != torch.float32:
         raise ValueError("scores must be float32 [B,Hkv,M]")
-    if tuple(evict_idx.shape) != (B, Hkv, T) or evict_idx.dtype != torch.int32:
+    if evict_idx.shape != (B, Hkv, T) or evict_idx.dtype != torch.int32:
         raise ValueError("evict_idx must be int32 [B,Hkv,T]")
     if scale is None:
         scale = d ** -0.5
@@ -423,20 +433,20 @@ def h2o_sdpa_chunk_backward(q, k_cache, v_cache, k_new, v_new, lse, dout, dq, dk
         if t.dtype != q.dtype:
             raise TypeError(f"{name} dtype {t.dtype} != q dtype {q.dtype}")
     for name, t in (("dout", dout), ("dq", dq)):
-        if tuple(t.shape) != (B, Hq, T, d):
+        if t.shape != (B, Hq, T, d):
             raise ValueError(f"{name} must be [B,Hq,T,d]")
     for name, t in (("k_cache", k_cache), ("v_cache", v_cache), ("dk_cache", dk_cache),
                     ("dv_cache", dv_cache)):
-        if tuple(t.shape) != (B, Hkv, M, d):
+        if t.shape != (B, Hkv, M, d):
             raise ValueError(f"{name} must be [B,Hkv,M,d]")
     if not cache:
         for name, t in (("k_new", k_new), ("v_new", v_new), ("dk_new", dk_new),
                         ("dv_new", dv_new)):
-            if t is None or t.dtype != q.dtype or tuple(t.shape) != (B, Hkv, T, d):
+            if t is None or t.dtype != q.dtype or t.shape != (B, Hkv, T, d):
                 raise ValueError(f"{name} must be [B,Hkv,T,d] in q's dtype")
-    elif token_pos.dtype != torch.int32 or tuple(token_pos.shape) != (B, Hkv, M):
+    elif token_pos.dtype != torch.int32 or token_pos.shape != (B, Hkv, M):
         raise ValueError("token_pos must be int32 [B,Hkv,M]")
-    if tuple(lse.shape) != (B, Hq, T) or lse.dtype != torch.float32:
+    if lse.shape != (B, Hq, T) or lse.dtype != torch.float32:
         raise ValueError("lse must be float32 [B,Hq,T]")
     if scale is None:
         scale = d ** -0.5
@@ -454,9 +464,9 @@ def h2o_sdpa_chunk_backward(q, k_cache, v_cache, k_new, v_new, lse, dout, dq, dk
 def _kv_rows(cache, idx, rows):
     B, Hkv, M, d = cache.shape
     k = idx.shape[2]
-    if idx.dtype != torch.int32 or tuple(idx.shape) != (B, Hkv, k):
+    if idx.dtype != torch.int32 or idx.shape != (B, Hkv, k):
         raise ValueError("idx must be int32 [B,Hkv,k]")
-    if rows.dtype != cache.dtype or tuple(rows.shape) != (B, Hkv, k, d):
+    if rows.dtype != cache.dtype or rows.shape != (B, Hkv, k, d):
         raise ValueError("rows must be [B,Hkv,k,d] in the cache's dtype")
     return B, Hkv, M, k, d
 
