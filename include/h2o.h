@@ -347,7 +347,8 @@ int h2o_debug_force_path(int path);
  * the recorded events and returns the summed duration (milliseconds) and the
  * launch count of kernel `id` since the last h2o_debug_timing call. Ids:
  *   0 generic lse pass   1 generic main pass   2 MFMA lse pass
- *   3 MFMA main pass     4 split reduce        5 column-sum reduce
+ *   3 MFMA main pass     4 split reduce (and the column-sum reduce with it)
+ *   5 column-sum reduce (alone)
  *   6 accumulate         7 bottom-k            8 insert
  *   9 decode split      10 decode combine     11 argmin + insert (k == 1)
  *  12 decode finish (h2o_chunk_step, T == 1)

@@ -24,6 +24,7 @@
 // 32-key K/V tile in LDS, so the K/V of a KV head is staged once for the G
 // query heads of its group. Tiles are triple buffered in LDS (see the
 // software pipeline below).
+#include "colsum.h"
 #include "internal.h"
 
 #include <climits>
@@ -859,13 +860,23 @@ __global__ __launch_bounds__(NW * 64) void main_pass(Geo g, int Hq, int Hkv, int
   }
 }
 
-// Sum of the per-split O partials, rounded to bf16.
+// The two reduces of a split main pass in one launch (they are independent):
+// the first ncol blocks add column partials (see colsum.h), the rest the
+// per-split O partials, in split order, rounded to bf16. One launch less, and
+// its start and end, matter at short chunks: the step 61.3 -> 58.7 us at B2 Hkv8
+// G4 d128 M8192 T37, 67.0 -> 65.1 at B3 Hkv16 G1 d64 M3001 T333.
 template <int D>
-__global__ __launch_bounds__(256) void split_reduce(const float* __restrict__ opart,
-                                                    bf16_t* __restrict__ out, int Hq, int Hkv,
-                                                    int G, int T, int R, int BH, int nsplit) {
-  const size_t e4 = (size_t)blockIdx.x * blockDim.x + threadIdx.x;   // group of 4 values
-  const size_t n4 = (size_t)BH * R * D / 4;
+__global__ __launch_bounds__(kColsumThreads) void reduce_partials(
+    ColsumArgs cs, int ncol_x, const float* __restrict__ opart, bf16_t* __restrict__ out, int Hq,
+    int Hkv, int R, int nsplit) {
+  const int ncol = ncol_x * cs.BH;
+  if ((int)blockIdx.x < ncol) {
+    colsum_reduce_block(cs, (int)blockIdx.x % ncol_x, (int)blockIdx.x / ncol_x);
+    return;
+  }
+  // group of 4 values
+  const size_t e4 = (size_t)(blockIdx.x - ncol) * kColsumThreads + threadIdx.x;
+  const size_t n4 = (size_t)cs.BH * R * D / 4;
   if (e4 >= n4) return;
   const size_t e = e4 * 4;
   const size_t bhr = e / D;
@@ -875,14 +886,14 @@ __global__ __launch_bounds__(256) void split_reduce(const float* __restrict__ op
   const int b = (int)(bh / Hkv), h = (int)(bh % Hkv);
   float4 s = make_float4(0.f, 0.f, 0.f, 0.f);
   for (int sp = 0; sp < nsplit; ++sp) {
-    const float4 v = *reinterpret_cast<const float4*>(opart + (size_t)sp * BH * R * D + e);
+    const float4 v = *reinterpret_cast<const float4*>(opart + (size_t)sp * cs.BH * R * D + e);
     s.x += v.x; s.y += v.y; s.z += v.z; s.w += v.w;
   }
-  const int i = r / G, gg = r % G;
+  const int i = r / cs.G, gg = r % cs.G;
   uint2 o;
   o.x = (uint32_t)f32_to_bf16(s.x) | ((uint32_t)f32_to_bf16(s.y) << 16);
   o.y = (uint32_t)f32_to_bf16(s.z) | ((uint32_t)f32_to_bf16(s.w) << 16);
-  *reinterpret_cast<uint2*>(out + ((size_t)(b * Hq + h * G + gg) * T + i) * D + dd) = o;
+  *reinterpret_cast<uint2*>(out + ((size_t)(b * Hq + h * cs.G + gg) * cs.T + i) * D + dd) = o;
 }
 
 // Both passes use 128-row blocks of 4 waves x 32 rows: few enough registers
@@ -951,10 +962,11 @@ hipError_t run(const Shape& s, const Plan& p, const void* q, const void* kc, con
   if (e != hipSuccess) return e;
   if (p.nsplit > 1) {
     const size_t n4 = (size_t)s.BH() * s.R() * s.d / 4;
-    e = launch_kernel(K_SPLIT_REDUCE, split_reduce<D>, dim3((unsigned)((n4 + 255) / 256)),
-                      dim3(256), st, (const float*)opart, (bf16_t*)out, s.Hq, s.Hkv, s.G(), s.T,
-                      s.R(), s.BH(), p.nsplit);
-    if (e != hipSuccess) return e;
+    const int ncol_x = (s.Nk() + kColsumThreads - 1) / kColsumThreads;
+    const size_t blocks = (size_t)ncol_x * s.BH() + (n4 + kColsumThreads - 1) / kColsumThreads;
+    return launch_kernel(K_SPLIT_REDUCE, reduce_partials<D>, dim3((unsigned)blocks),
+                         dim3(kColsumThreads), st, colsum_args(s, p, parts, wsum, acc), ncol_x,
+                         (const float*)opart, (bf16_t*)out, s.Hq, s.Hkv, s.R(), p.nsplit);
   }
   return launch_colsum_reduce(s, p, parts, wsum, st, acc);
 }

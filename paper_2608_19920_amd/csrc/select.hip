@@ -1,60 +1,13 @@
 // Column-sum reduce, H2O score accumulation, bottom-k selection and insert.
+#include "colsum.h"
 #include "internal.h"
 
 namespace h2o {
 namespace {
 
 // ------------------------------------------------------------ colsum reduce
-// wsum[bh][j] = sum over the partial slots p (in increasing p, so the result
-// is bitwise reproducible) whose rows can see column j. With scores
-// non-null, a chunk step's accumulation in the same pass: scores[bh][j] +=
-// wsum[bh][j] for j < M, one float32 addition of the stored value (the bits
-// of the separate accumulate kernel); with copy non-null the sum is also
-// written to copy[bh][j], the ranking input of the fused selection.
-__global__ __launch_bounds__(256) void colsum_reduce_kernel(const float* __restrict__ parts,
-                                                            float* __restrict__ wsum,
-                                                            float* __restrict__ scores,
-                                                            float* __restrict__ copy, int nparts,
-                                                            int rows_per_part, int BH, int Nk,
-                                                            int ld, int G, int T, int M,
-                                                            int Tk) {
-  const int j = blockIdx.x * blockDim.x + threadIdx.x;
-  const int bh = blockIdx.y;
-  if (j >= Nk) return;
-  // the score is requested with the partials, not after them
-  float* sc = scores && j < M ? scores + (size_t)bh * M + j : nullptr;
-  const float s_old = sc ? *sc : 0.f;
-  // The partials that see column j are p0 .. nparts-1 (kv_end grows with
-  // p): all of them for a cache column, and for chunk key i = j - M those
-  // whose last row (r1 - 1) / G reaches i, i.e. (p + 1) * rows_per_part > i * G.
-  int p0 = 0;
-  if (Tk > 0 && j >= M) p0 = ((j - M) * G) / rows_per_part;
-  const float* src = parts + ((size_t)p0 * BH + bh) * ld + j;
-  const size_t stride = (size_t)BH * ld;
-  float s = 0.f;
-  int p = p0;
-  // sixteen loads in flight, additions in increasing p (bitwise reproducible)
-  for (; p + 15 < nparts; p += 16, src += 16 * stride) {
-    float a[16];
-#pragma unroll
-    for (int e = 0; e < 16; ++e) a[e] = src[e * stride];
-#pragma unroll
-    for (int e = 0; e < 16; ++e) s += a[e];
-  }
-  for (; p + 3 < nparts; p += 4, src += 4 * stride) {
-    const float a0 = src[0], a1 = src[stride], a2 = src[2 * stride], a3 = src[3 * stride];
-    s += a0;
-    s += a1;
-    s += a2;
-    s += a3;
-  }
-  for (; p < nparts; ++p, src += stride) s += src[0];
-  wsum[(size_t)bh * Nk + j] = s;
-  if (sc) {
-    const float acc = s_old + s;
-    *sc = acc;
-    if (copy) copy[(size_t)bh * M + j] = acc;
-  }
+__global__ __launch_bounds__(256) void colsum_reduce_kernel(ColsumArgs a) {
+  colsum_reduce_block(a, blockIdx.x, blockIdx.y);
 }
 
 // ---------------------------------------------------------------- accumulate
@@ -675,10 +628,9 @@ hipError_t launch_broadcast_rows(const int32_t* src, int32_t* dst, int B, int n,
 
 hipError_t launch_colsum_reduce(const Shape& s, const Plan& p, const float* parts, float* wsum,
                                 hipStream_t st, ScoreAcc acc) {
-  dim3 grid((s.Nk() + 255) / 256, s.BH());
-  return launch_kernel(K_COLSUM_REDUCE, colsum_reduce_kernel, grid, dim3(256), st, parts, wsum,
-                       acc.scores, acc.scores ? acc.copy : nullptr, p.nparts, p.rows_per_part,
-                       s.BH(), s.Nk(), p.parts_ld, s.G(), s.T, s.M, s.Tk());
+  return launch_kernel(K_COLSUM_REDUCE, colsum_reduce_kernel,
+                       dim3((s.Nk() + kColsumThreads - 1) / kColsumThreads, s.BH()),
+                       dim3(kColsumThreads), st, colsum_args(s, p, parts, wsum, acc));
 }
 
 hipError_t launch_accumulate(float* scores, const float* wsum, int rows, int M, int T,
