@@ -224,7 +224,8 @@ struct ScoreScan {
   }
 };
 
-template <int D, int G, bool CACHE, bool INS>
+// NT: the K and V loads are non-temporal.
+template <int D, int G, bool CACHE, bool INS, bool NT>
 __device__ __forceinline__ void split_body(
     const bf16_t* __restrict__ q, const bf16_t* __restrict__ kc, const bf16_t* __restrict__ vc,
     int Hq, int Hkv, int M, float c_log2, float* __restrict__ logits,
@@ -236,6 +237,7 @@ __device__ __forceinline__ void split_body(
   constexpr int RPL = 512 / D;               // V rows per wave load
   constexpr int NV = kStep / RPL;            // V loads per step
   constexpr int VP = vpitch<D>();
+  constexpr int kAux = NT ? 2 : 0;           // cache policy of the K and V loads (2: nt)
   static_assert(G <= 16 && (D == 64 || D == 128), "decode shape");
   __shared__ __attribute__((aligned(16))) bf16_t vs_all[kWaves][kStep * VP];
   __shared__ float red_m[kWaves][16], red_l[kWaves][16];
@@ -286,12 +288,12 @@ __device__ __forceinline__ void split_body(
       for (int dh = 0; dh < DH; ++dh)
         kr[u][kb * DH + dh] = __builtin_bit_cast(
             u32x4, __builtin_amdgcn_raw_buffer_load_b128(
-                       krs, (int)(base + koff + (uint32_t)((16 * kb * D + 32 * dh) * 2)), 0, 0));
+                       krs, (int)(base + koff + (uint32_t)((16 * kb * D + 32 * dh) * 2)), 0, kAux));
 #pragma unroll
     for (int t = 0; t < NV; ++t)
       vr[u][t] = __builtin_bit_cast(
           u32x4, __builtin_amdgcn_raw_buffer_load_b128(
-                     vrs, (int)(base + voff + (uint32_t)(t * RPL * D * 2)), 0, 0));
+                     vrs, (int)(base + voff + (uint32_t)(t * RPL * D * 2)), 0, kAux));
   };
 
   bf16x8 qb[DH];
@@ -483,30 +485,30 @@ __device__ __forceinline__ void split_body(
       int Hq, int Hkv, int M, float c_log2, float *__restrict__ logits,                       \
       float2 *__restrict__ dstat, float *__restrict__ dO, float *__restrict__ sink,           \
       const int32_t *__restrict__ tp, int32_t pos0, InsArgs ins
-template <int D, int G>
+template <int D, int G, bool NT>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(D == 64 ? 4 : 1)))
 void decode_split(H2O_SPLIT_PARAMS) {
-  split_body<D, G, false, false>(q, kc, vc, Hq, Hkv, M, c_log2, logits, dstat, dO, sink, tp,
+  split_body<D, G, false, false, NT>(q, kc, vc, Hq, Hkv, M, c_log2, logits, dstat, dO, sink, tp,
                                  pos0, ins);
 }
-template <int D, int G>
+template <int D, int G, bool NT>
 __global__ __launch_bounds__(kThreads) void decode_split_cache(H2O_SPLIT_PARAMS) {
-  split_body<D, G, true, false>(q, kc, vc, Hq, Hkv, M, c_log2, logits, dstat, dO, sink, tp, pos0,
+  split_body<D, G, true, false, NT>(q, kc, vc, Hq, Hkv, M, c_log2, logits, dstat, dO, sink, tp, pos0,
                                 ins);
 }
-template <int D, int G>
+template <int D, int G, bool NT>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(D == 64 ? 3 : 1)))
 void decode_split_ins(H2O_SPLIT_PARAMS) {
-  split_body<D, G, true, true>(q, kc, vc, Hq, Hkv, M, c_log2, logits, dstat, dO, sink, tp, pos0,
+  split_body<D, G, true, true, NT>(q, kc, vc, Hq, Hkv, M, c_log2, logits, dstat, dO, sink, tp, pos0,
                                ins);
 }
 #undef H2O_SPLIT_PARAMS
 
 template <int D, int G, bool CACHE, bool INS>
 const void* split_kernel() {
-  if constexpr (INS) return reinterpret_cast<const void*>(decode_split_ins<D, G>);
-  else if constexpr (CACHE) return reinterpret_cast<const void*>(decode_split_cache<D, G>);
-  else return reinterpret_cast<const void*>(decode_split<D, G>);
+  if constexpr (INS) return reinterpret_cast<const void*>(decode_split_ins<D, G, false>);
+  else if constexpr (CACHE) return reinterpret_cast<const void*>(decode_split_cache<D, G, false>);
+  else return reinterpret_cast<const void*>(decode_split<D, G, false>);
 }
 
 // ------------------------------------------------------------------ combine
@@ -973,29 +975,37 @@ int split_count(int M, int BH) {
   return ns < 1 ? 1 : ns;
 }
 
+// K and V bytes of a call from which its loads are non-temporal. A cache is read
+// once per call, in full: what of it should stay in the 256 MB Infinity Cache
+// depends on what else the caller's step reads, which is not known here, so a
+// call leaves that to the hardware until three such caches no longer fit.
+// Measured on three caches in turn (default / nt, us a step, G = 4): B10 M4096 d64
+// (84 MB) 23.4 / 26.0, B12 (101 MB) 30.2 / 29.1, B24 55.0 / 52.7; B4 Hkv8 d128 M32768
+// (537 MB) 124.5 / 117.2, insert-first 127 / 119; B8 Hkv16 d128 M16384 (1.07 GB)
+// 217 / 195.
+constexpr size_t kNtBytes = size_t(96) << 20;
+
 // ins.scores non-null: the fused insert-first form (cache mode).
 template <int D, int G>
 hipError_t launch_split(hipStream_t st, int BH, const void* q, const void* kc, const void* vc,
                         int Hq, int Hkv, int M, float c, float* logits, float2* dstat, float* dO,
                         float* sink, KeyPos kp, int* ns, InsArgs ins) {
+  const bool nt = (size_t)BH * (size_t)M * (size_t)(4 * D) >= kNtBytes;
+  auto go = [&](auto kern, auto kern_nt) {
+    return launch_kernel(K_DECODE_SPLIT, nt ? kern_nt : kern, dim3(*ns, BH), dim3(kThreads), st,
+                         (const bf16_t*)q, (const bf16_t*)kc, (const bf16_t*)vc, Hq, Hkv, M, c,
+                         logits, dstat, dO, sink, kp.tp, kp.pos0, ins);
+  };
   if (kp.tp && ins.scores) {
     *ns = split_count<D, G, true, true>(M, BH);
-    return launch_kernel(K_DECODE_SPLIT, decode_split_ins<D, G>, dim3(*ns, BH),
-                         dim3(kThreads), st, (const bf16_t*)q, (const bf16_t*)kc,
-                         (const bf16_t*)vc, Hq, Hkv, M, c, logits, dstat, dO, sink, kp.tp,
-                         kp.pos0, ins);
+    return go(decode_split_ins<D, G, false>, decode_split_ins<D, G, true>);
   }
   if (kp.tp) {
     *ns = split_count<D, G, true>(M, BH);
-    return launch_kernel(K_DECODE_SPLIT, decode_split_cache<D, G>, dim3(*ns, BH),
-                         dim3(kThreads), st, (const bf16_t*)q, (const bf16_t*)kc,
-                         (const bf16_t*)vc, Hq, Hkv, M, c, logits, dstat, dO, sink, kp.tp,
-                         kp.pos0, ins);
+    return go(decode_split_cache<D, G, false>, decode_split_cache<D, G, true>);
   }
   *ns = split_count<D, G, false>(M, BH);
-  return launch_kernel(K_DECODE_SPLIT, decode_split<D, G>, dim3(*ns, BH), dim3(kThreads),
-                       st, (const bf16_t*)q, (const bf16_t*)kc, (const bf16_t*)vc, Hq, Hkv, M, c,
-                       logits, dstat, dO, sink, (const int32_t*)nullptr, (int32_t)0, ins);
+  return go(decode_split<D, G, false>, decode_split<D, G, true>);
 }
 
 }  // namespace

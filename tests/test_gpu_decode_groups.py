@@ -17,9 +17,11 @@ pytestmark = pytest.mark.gpu
 STEP = [  # B, Hq, Hkv, d, M
     (1, 7, 1, 128, 4097), (2, 16, 2, 128, 6145), (1, 3, 1, 64, 4096), (1, 10, 2, 64, 4099),
     (1, 6, 1, 128, 33), (1, 7, 1, 64, 8192), (1, 8, 1, 128, 1), (1, 5, 1, 128, 2049),
-    (1, 2, 2, 128, 140000),           # over 64 candidate blocks a head
+    (1, 2, 2, 128, 140000),           # over 64 candidate blocks a head; 143 MB: non-temporal loads
+    (1, 14, 2, 128, 98304),           # 96 MiB of K and V, the least with non-temporal loads
 ]
-INSERT = [(1, 7, 1, 128, 4097), (2, 14, 2, 64, 8200), (1, 16, 2, 128, 12289), (1, 4, 1, 128, 4096)]
+INSERT = [(1, 7, 1, 128, 4097), (2, 14, 2, 64, 8200), (1, 16, 2, 128, 12289), (1, 4, 1, 128, 4096),
+          (1, 8, 2, 128, 98305)]   # non-temporal loads
 
 
 def _inputs(B, Hq, Hkv, d, M):
