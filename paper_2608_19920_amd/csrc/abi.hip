@@ -375,6 +375,9 @@ hipError_t launch_evict(int policy, void* k_cache, void* v_cache, float* scores,
   int key_rows = 0;
   float* wk = reinterpret_cast<float*>(ews);
   hipError_t e = hipSuccess;
+  if (policy == H2O_POLICY_NORM && k == 1)   // the argmin divides by the ages itself
+    return launch_argmin_insert(k_cache, v_cache, scores, scores, 0, token_pos, t, token_pos,
+                                k_new, v_new, wsum, evict_idx, rows, M, T, d, pos0, eb, st);
   if (policy == H2O_POLICY_NORM) {
     e = launch_norm_keys(scores, token_pos, wk, rows, M, t, st);
     keys = wk;
@@ -385,8 +388,12 @@ hipError_t launch_evict(int policy, void* k_cache, void* v_cache, float* scores,
   }
   if (e != hipSuccess) return e;
   if (k == 1)
-    return launch_argmin_insert(k_cache, v_cache, scores, keys, key_rows, token_pos, k_new,
-                                v_new, wsum, evict_idx, rows, M, T, d, pos0, eb, st);
+    return launch_argmin_insert(k_cache, v_cache, scores, keys, key_rows, nullptr, 0, token_pos,
+                                k_new, v_new, wsum, evict_idx, rows, M, T, d, pos0, eb, st);
+  // the norm keys are an array of their own: ranking and insert in one launch
+  if (policy == H2O_POLICY_NORM && bottomk_insert_supported(k))
+    return launch_bottomk_insert(keys, scores, token_pos, k_cache, v_cache, k_new, v_new, wsum,
+                                 evict_idx, rows, M, T, d, k, pos0, eb, st);
   if (policy == H2O_POLICY_ORIG) {
     int32_t* head_idx = reinterpret_cast<int32_t*>(ews + align256((size_t)Hkv * M * 4));
     e = launch_bottomk(keys, Hkv, M, k, head_idx, st);
@@ -518,8 +525,8 @@ int chunk_step(StepPart part, const void* q, void* k_cache, void* v_cache, float
       if (e == hipSuccess && part == STEP_EVICT)
         e = launch_accumulate(scores, wsum, rows, M, T, st);
       if (e == hipSuccess && T == 1) {
-        e = launch_argmin_insert(k_cache, v_cache, scores, scores, 0, token_pos, k_new, v_new,
-                                 wsum, evict_idx, rows, M, T, d, pos0, eb, st);
+        e = launch_argmin_insert(k_cache, v_cache, scores, scores, 0, nullptr, 0, token_pos, k_new,
+                                 v_new, wsum, evict_idx, rows, M, T, d, pos0, eb, st);
       } else if (e == hipSuccess && fused) {
         e = launch_bottomk_insert(keys, scores, token_pos, k_cache, v_cache, k_new, v_new, wsum,
                                   evict_idx, rows, M, T, d, T, pos0, eb, st);

@@ -226,7 +226,8 @@ hipError_t launch_bottomk_insert(const float* keys, float* scores, int32_t* toke
                                  int32_t* idx, int rows, int M, int T, int d, int k,
                                  int32_t pos0, int elem_bytes, hipStream_t st);
 hipError_t launch_argmin_insert(void* kc, void* vc, float* scores, const float* keys,
-                                int key_rows, int32_t* token_pos, const void* kn, const void* vn,
+                                int key_rows, const int32_t* age_pos, int32_t t,
+                                int32_t* token_pos, const void* kn, const void* vn,
                                 const float* wsum, int32_t* idx, int rows, int M, int T, int d,
                                 int32_t pos0, int elem_bytes, hipStream_t st);
 // Score variants: the ranked keys (h2o_norm per row, h2o_orig per kv head)

@@ -482,41 +482,52 @@ __global__ __launch_bounds__(kInsThreads) void insert_kernel(
 }
 
 // k == 1 (token generation): the (score, slot)-smallest slot of each row and
-// the insert into it, one block per row.
-constexpr int kArgThreads = 256;
-
+// the insert into it, one block of NT threads per row.
+//
 // The ranked values come from `keys` (the scores themselves, or a score
 // variant), row `row` or, with key_rows > 0, row `row % key_rows` (one key
-// row shared by the batch).
-__global__ __launch_bounds__(kArgThreads) void argmin_insert_kernel(
+// row shared by the batch). With age_pos non-null they are the keys over the
+// slots' ages t - age_pos (h2o_norm: norm_keys_kernel's division, in the
+// launch that ranks them).
+// Bound by latency: sixteen keys per thread are requested before the first is
+// used, and rows of more than 4,096 slots (one round of 256 threads) take
+// 1,024 threads. Against 256 threads, four keys ahead and norm_keys_kernel
+// before it: 16 rows of 30,000 slots with ages 18.6 -> 10.9 us, 64 rows of
+// 2,215 8.7 -> 5.2; without ages 16 rows of 13,511 8.5 -> 6.0.
+template <int NT>
+__global__ __launch_bounds__(NT) void argmin_insert_kernel(
     uint4* __restrict__ kc, uint4* __restrict__ vc, float* scores, const float* keys,
-    int key_rows, int32_t* __restrict__ token_pos, const uint4* __restrict__ kn,
-    const uint4* __restrict__ vn, const float* __restrict__ wsum, int32_t* __restrict__ idx,
-    int M, int T, int vecs, int32_t pos0) {
-  __shared__ uint32_t red_hi[kArgThreads / 64], red_lo[kArgThreads / 64];
+    int key_rows, const int32_t* age_pos, int32_t t, int32_t* token_pos,
+    const uint4* __restrict__ kn, const uint4* __restrict__ vn, const float* __restrict__ wsum,
+    int32_t* __restrict__ idx, int M, int T, int vecs, int32_t pos0) {
+  __shared__ uint32_t red_hi[NT / 64], red_lo[NT / 64];
   __shared__ int sh_slot;
   const size_t row = blockIdx.x;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const float* s = keys + (key_rows > 0 ? row % key_rows : row) * M;
+  const int32_t* ap = age_pos ? age_pos + row * M : nullptr;
   // (key, slot), lexicographic; the start (max key, slot 0) is a real pair
   // whenever every key is the maximum, so the result is always a slot
   uint32_t bk = 0xFFFFFFFFu, bj = 0u;
-  // four independent loads per step; slots are visited in increasing order
-  // per thread, so a strict < keeps the lowest slot among equal keys
-  int j = tid;
-  for (; j + 3 * kArgThreads < M; j += 4 * kArgThreads) {
-    float v[4];
+  // slots are visited in increasing order per thread, so a strict < keeps the
+  // lowest slot among equal keys
+  constexpr int U = 16;
+  for (int j0 = tid; j0 < M; j0 += U * NT) {
+    float v[U];
+    int32_t a[U];
 #pragma unroll
-    for (int u = 0; u < 4; ++u) v[u] = s[j + u * kArgThreads];
+    for (int u = 0; u < U; ++u) v[u] = j0 + u * NT < M ? s[j0 + u * NT] : 0.f;
+    if (ap) {   // uniform
 #pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      const uint32_t key = order_key(v[u]);
-      if (key < bk) { bk = key; bj = (uint32_t)(j + u * kArgThreads); }
+      for (int u = 0; u < U; ++u) a[u] = j0 + u * NT < M ? ap[j0 + u * NT] : 0;
+#pragma unroll
+      for (int u = 0; u < U; ++u) v[u] = v[u] / (float)(t - a[u]);
     }
-  }
-  for (; j < M; j += kArgThreads) {
-    const uint32_t key = order_key(s[j]);
-    if (key < bk) { bk = key; bj = (uint32_t)j; }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const uint32_t key = order_key(v[u]);
+      if (j0 + u * NT < M && key < bk) { bk = key; bj = (uint32_t)(j0 + u * NT); }
+    }
   }
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) {
@@ -526,7 +537,7 @@ __global__ __launch_bounds__(kArgThreads) void argmin_insert_kernel(
   if (lane == 0) { red_hi[wave] = bk; red_lo[wave] = bj; }
   __syncthreads();
   if (tid == 0) {
-    for (int w = 1; w < kArgThreads / 64; ++w)
+    for (int w = 1; w < NT / 64; ++w)
       if (red_hi[w] < bk || (red_hi[w] == bk && red_lo[w] < bj)) { bk = red_hi[w]; bj = red_lo[w]; }
     const int slot = (int)bj;
     sh_slot = slot;
@@ -539,7 +550,7 @@ __global__ __launch_bounds__(kArgThreads) void argmin_insert_kernel(
   __syncthreads();
   const int slot = sh_slot;
   if ((unsigned)slot >= (unsigned)M) return;
-  for (int c = tid; c < vecs; c += kArgThreads) {
+  for (int c = tid; c < vecs; c += NT) {
     kc[(row * M + slot) * vecs + c] = kn[(row * T) * vecs + c];
     vc[(row * M + slot) * vecs + c] = vn[(row * T) * vecs + c];
   }
@@ -548,14 +559,18 @@ __global__ __launch_bounds__(kArgThreads) void argmin_insert_kernel(
 }  // namespace
 
 hipError_t launch_argmin_insert(void* kc, void* vc, float* scores, const float* keys,
-                                int key_rows, int32_t* token_pos, const void* kn, const void* vn,
+                                int key_rows, const int32_t* age_pos, int32_t t,
+                                int32_t* token_pos, const void* kn, const void* vn,
                                 const float* wsum, int32_t* idx, int rows, int M, int T, int d,
                                 int32_t pos0, int elem_bytes, hipStream_t st) {
   if (rows == 0) return hipSuccess;
-  return launch_kernel(K_ARGMIN_INSERT, argmin_insert_kernel, dim3(rows), dim3(kArgThreads), st,
-                       (uint4*)kc, (uint4*)vc, scores, keys, key_rows, token_pos,
-                       (const uint4*)kn, (const uint4*)vn, wsum, idx, M, T,
-                       d * elem_bytes / 16, pos0);
+  auto go = [&](auto kern, int threads) {
+    return launch_kernel(K_ARGMIN_INSERT, kern, dim3(rows), dim3(threads), st, (uint4*)kc,
+                         (uint4*)vc, scores, keys, key_rows, age_pos, t, token_pos,
+                         (const uint4*)kn, (const uint4*)vn, wsum, idx, M, T,
+                         d * elem_bytes / 16, pos0);
+  };
+  return M > 4096 ? go(argmin_insert_kernel<1024>, 1024) : go(argmin_insert_kernel<256>, 256);
 }
 
 // ------------------------------------------------------- score variants
