@@ -13,12 +13,11 @@
 // Rows passes: a wave owns 32 packed rows (their Q and dO are B operands in
 // registers); the block's waves share 64-key K/V tiles in LDS; the
 // transposed K operand of the dQ product comes from ds_read_b64_tr_b16.
-// Keys pass: two waves own 32 keys, one for S, P and dV, one for dP, dS and dK,
-// and all waves of a block share 32-row Q/dO tiles. S and dP are computed in
-// the key-per-lane orientation, so P and dS leave the accumulators already
-// laid out as the B operands of the dV and dK products (two 16-row blocks per
-// operand), and the transposed dO and Q operands again come from transposing
-// LDS reads.
+// Keys pass: a wave owns 16 keys, and all waves of a block share Q/dO tiles of
+// 64 or 32 rows. S and dP are computed in the key-per-lane orientation, so P
+// and dS leave the accumulators already laid out as the B operands of the dV
+// and dK products (two 16-row blocks per operand), and the transposed dO and Q
+// operands again come from transposing LDS reads.
 // When the rows passes would have too few blocks to fill the CUs they split
 // the key range: D partials are summed in split order (the dq pass's first
 // split leaves the sum for the keys pass), dq partials are float32 and
@@ -45,6 +44,15 @@ constexpr int kNT = 64 * kW;   // threads per block
 // and at GQA 7:1 (B2 Hkv4 M16384 T2048): D pass 168 -> 159 and 1,302 -> 1,222 us,
 // keys pass 408 -> 397 and 2,464 -> 2,395, dq pass unchanged.
 constexpr int kTile = 64;
+// The keys pass takes 32-row tiles up to this many packed rows: at d = 128 where
+// half of a 64-row tile would be empty (14 rows, B3 Hkv16 M2355: 32.0 -> 28.8 us;
+// 40 and 64 rows 32.4 -> 34.6 and 33.0 -> 35.4), at d = 64 also where a fourth
+// block per CU (128 registers; 3 blocks with 64-row tiles) is worth more than
+// the barriers: 14 rows 18.2 -> 16.6, 160 28.8 -> 25.0, 250 35.3 -> 33.8, 512 (B4
+// Hkv16 M4096) 119 -> 113, 1,200 (B2 Hkv8 M8192) 120 -> 116, but 4,096 (B1 Hkv8
+// M8192) 224 -> 238 and 7,168 (B2 Hkv4 M16384) 677 -> 678.
+template <int D>
+constexpr int kShortRows = D == 64 ? 1536 : 32;
 constexpr int kPad = 16;       // bf16 past d per LDS row (pitch 288 B at d = 128)
 constexpr int kRB = kW * 32;   // packed rows per block of the rows passes (32 per wave)
 
@@ -439,9 +447,9 @@ __global__ __launch_bounds__(NW * 64) void bwd_rows(BArgs a) {
 
 // ------------------------------------------------------------------ keys pass
 // A wave owns NKB*16 keys (NKB key blocks of 16).
-template <int D, int NKB, bool CACHE, int NW = kW>
+template <int D, int NKB, bool CACHE, int ROWS, int NW = kW>
 __global__ __launch_bounds__(NW * 64) void bwd_keys(BArgs a) {
-  constexpr int NT = NW * 64, ROWS = kTile;
+  constexpr int NT = NW * 64;
   constexpr int P = pitch<D>(), KS = D / 32, NL = tile_chunks<D, NT, ROWS>();
   __shared__ __attribute__((aligned(16))) bf16_t Qs[2][ROWS * P];
   __shared__ __attribute__((aligned(16))) bf16_t Os[2][ROWS * P];
@@ -639,14 +647,13 @@ hipError_t run(const Shape& s, const BackwardPlan& pl, BArgs a, hipStream_t st) 
   }
   if (s.Nk() == 0) return hipSuccess;
   const dim3 gkeys((s.Nk() + kW * 16 - 1) / (kW * 16), BH);
-  return launch_kernel(K_BWD_DKDV, bwd_keys<D, 1, CACHE>, gkeys, dim3(kNT), st, a);
+  if (s.R() <= kShortRows<D>)
+    return launch_kernel(K_BWD_DKDV, bwd_keys<D, 1, CACHE, 32>, gkeys, dim3(kNT), st, a);
+  return launch_kernel(K_BWD_DKDV, bwd_keys<D, 1, CACHE, kTile>, gkeys, dim3(kNT), st, a);
 }
 
 }  // namespace
 
-#ifndef H2O_DOT8_PER_CU
-#define H2O_DOT8_PER_CU 1
-#endif
 // Splits of the key range of the two rows passes, so that their grids fill
 // the CUs (two 4-wave blocks per CU, three for the D pass at d = 64);
 // at least 8 times 32 keys per split. At d = 128 either pass runs 8-wave blocks
@@ -677,8 +684,8 @@ BackwardPlan backward_plan(const Shape& s, int dtype) {
         p.ns_dq = ns8;
       }
       // the D pass likewise (one 8-wave block per CU)
-      const int nsd8 = pick(blocks8, H2O_DOT8_PER_CU * cus);
-      if (H2O_DOT8_PER_CU > 0 && blocks8 * nsd8 % (H2O_DOT8_PER_CU * cus) == 0) {
+      const int nsd8 = pick(blocks8, cus);
+      if (blocks8 * nsd8 % cus == 0) {
         p.dot_waves = 8;
         p.ns_dot = nsd8;
       }
