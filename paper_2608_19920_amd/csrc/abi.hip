@@ -390,8 +390,10 @@ hipError_t launch_evict(int policy, void* k_cache, void* v_cache, float* scores,
   if (k == 1)
     return launch_argmin_insert(k_cache, v_cache, scores, keys, key_rows, nullptr, 0, token_pos,
                                 k_new, v_new, wsum, evict_idx, rows, M, T, d, pos0, eb, st);
-  // the norm keys are an array of their own: ranking and insert in one launch
-  if (policy == H2O_POLICY_NORM && bottomk_insert_supported(k))
+  // ranking and insert in one launch: the norm keys are an array of their own
+  if (policy == H2O_POLICY_NORM ? bottomk_insert_supported(k)
+                                : policy == H2O_POLICY_H2O &&
+                                      bottomk_insert_in_place(M, k, d, eb))
     return launch_bottomk_insert(keys, scores, token_pos, k_cache, v_cache, k_new, v_new, wsum,
                                  evict_idx, rows, M, T, d, k, pos0, eb, st);
   if (policy == H2O_POLICY_ORIG) {

@@ -217,10 +217,12 @@ hipError_t launch_accumulate(float* scores, const float* wsum, int rows, int M, 
                              hipStream_t st);
 hipError_t launch_bottomk(const float* scores, int rows, int M, int k, int32_t* idx,
                           hipStream_t st);
-// Bottom-k of keys (row pitch M; not written while the kernel runs, and
-// another array than scores) and the insert of the chunk (as launch_insert)
-// in one launch, for the k that bottomk_insert_supported() accepts.
+// Bottom-k of keys (row pitch M; not written while the kernel runs) and the
+// insert of the chunk (as launch_insert) in one launch, for the k that
+// bottomk_insert_supported() accepts. The keys are another array than scores,
+// or the scores themselves where bottomk_insert_in_place() allows it.
 bool bottomk_insert_supported(int k);
+bool bottomk_insert_in_place(int M, int k, int d, int elem_bytes);
 hipError_t launch_bottomk_insert(const float* keys, float* scores, int32_t* token_pos, void* kc,
                                  void* vc, const void* kn, const void* vn, const float* wsum,
                                  int32_t* idx, int rows, int M, int T, int d, int k,

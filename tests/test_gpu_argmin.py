@@ -1,6 +1,6 @@
-"""Evictions of one token (argmin and insert in one launch) and h2o_norm's
-ranking with its insert, bit-exact against the oracle where the argmin changes
-its block shape or starts another round of loads."""
+"""Evictions of one token (argmin and insert in one launch) and rankings of
+several tokens that share a launch with their insert, bit-exact against the oracle where the kernels
+change their block shape, start another round of loads or stop applying."""
 import pytest
 
 from test_gpu_variants import POLICIES, _assert_same, _evict_inputs, _expect, _run_evict
@@ -30,3 +30,17 @@ def test_norm_rows_edges(M, T):
     say(f"norm M{M} T{T}")
     x = _evict_inputs(B, Hkv, M, T, d, dt, 1, seed=M + T)
     _assert_same(_run_evict(x, T, dt, "h2o_norm"), _expect(x, T, "h2o_norm"), "h2o_norm")
+
+
+@pytest.mark.parametrize("M,T,d,dt", [
+    (2, 2, 64, "bf16"), (600, 128, 64, "bf16"), (600, 129, 64, "bf16"),
+    (300, 64, 128, "bf16"), (300, 65, 128, "bf16"), (32, 32, 128, "f32"), (200, 33, 128, "f32"),
+    (32768, 40, 64, "bf16"), (32769, 40, 64, "bf16"), (1027, 3, 128, "f32"),
+])
+def test_scores_ranked_in_place(M, T, d, dt):
+    """h2o: one launch while the chunk is one 16-byte vector per thread (1,024) and
+    the row fits LDS (32,768 slots), two beyond."""
+    say(f"in place M{M} T{T} d{d} {dt}")
+    for quant in (None, 1):
+        x = _evict_inputs(2, 3, M, T, d, dt, quant, seed=M + T)
+        _assert_same(_run_evict(x, T, dt, "h2o"), _expect(x, T, "h2o"), "h2o")
