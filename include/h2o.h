@@ -192,9 +192,10 @@ int h2o_evict_insert_policy(void* k_cache, void* v_cache, float* scores,
  * chunk). Arguments and results are those of the three calls (same bits);
  * every buffer they read or write is an argument here, the workspace is the
  * one h2o_workspace_bytes() sizes, and M >= T. For T == 1 in bf16 the step
- * is two kernel launches: the split attention kernel, then one block per KV
- * head that merges the splits, accumulates the scores, picks the slot and
- * inserts; other shapes run the kernels of the three calls in order. */
+ * is two kernel launches: the split attention kernel, then one kernel that
+ * merges the splits, accumulates the scores, picks each KV head's slot and
+ * inserts (above 4,096 slots the picking and inserting is a third launch); other
+ * shapes run the kernels of the three calls in order. */
 int h2o_chunk_step(const void* q, void* k_cache, void* v_cache, float* scores,
                    int32_t* token_pos, const void* k_new, const void* v_new,
                    void* out, float* lse, float* wsum, int32_t* evict_idx,
@@ -209,8 +210,9 @@ int h2o_chunk_step(const void* q, void* k_cache, void* v_cache, float* scores,
  * fixed array of h2o_noalloc_scratch_bytes() bytes (32 MiB) inside the
  * library instead: one array per GPU the library runs on, held until the
  * process ends. No call allocates or frees memory. A shape whose
- * h2o_workspace_bytes() exceeds the array returns H2O_EWORKSPACE before
- * anything is enqueued (the decode shape B8 Hq32 Hkv8 d64 M4096 needs about
+ * h2o_workspace_bytes() exceeds the array runs a plan that needs less (fewer
+ * splits, the generic kernels for float32; its sums round differently), and
+ * returns H2O_EWORKSPACE before anything is enqueued when none fits (the decode shape B8 Hq32 Hkv8 d64 M4096 needs about
  * 8 MiB). Every call on one GPU shares that GPU's array, and the array keeps
  * what the last call left there (no kernel reads it before writing it), so
  * calls that can overlap on one GPU - different streams, host threads -
@@ -356,7 +358,7 @@ int h2o_debug_force_path(int path);
  *  14 backward dQ (VALU: and the rows' D)  15 backward dK/dV
  *  16 KV gather / scatter   17 backward rows' D (MFMA path)
  *  18 backward dQ split reduce (MFMA path)
- *  19 bottom-k and insert in one launch (h2o_chunk_step, 1 < T <= 4096)
+ *  19 bottom-k and insert in one launch (1 < k <= 4096)
  *  20 float32 attention (matrix cores)
  *  21 decode argmin and insert (h2o_chunk_step, T == 1, long caches) */
 int h2o_debug_timing(int on);

@@ -39,8 +39,8 @@ KERNELS = {
     "decode_finish": ("decode_finish<", ["decode.hip"]),
     "mfma_lse": ("lse_pass<", ["sdpa_mfma.hip"]),
     "mfma_main": ("main_pass<", ["sdpa_mfma.hip"]),
-    "split_reduce": ("split_reduce<", ["sdpa_mfma.hip"]),
-    "colsum_reduce": ("colsum_reduce_kernel", ["select.hip"]),
+    "split_reduce": ("reduce_partials<", ["sdpa_mfma.hip", "colsum.h"]),
+    "colsum_reduce": ("colsum_reduce_kernel", ["select.hip", "colsum.h"]),
     "bottomk": ("bottomk_kernel<", ["select.hip"]),
     "bottomk_insert": ("bottomk_insert_kernel<", ["select.hip"]),
     "insert": ("::insert_kernel(", ["select.hip"]),

@@ -9,9 +9,13 @@
 //            and read back transposed. The split's softmax partial (m, l,
 //            O-partial) per query head is written out, and so are the float32
 //            logits for the column sums ([bh][g][slot]).
-//   combine  block bh merges the splits with the chunk's own key (column M),
-//            writes out and lse, and wsum[j] = sum_g exp2(logit_gj - lambda_g)
-//            from the stored logits.
+//   combine  merges the splits with the chunk's own key (column M): blocks over
+//            the slots write wsum[j] = sum_g exp2(logit_gj - lambda_g) from the
+//            stored logits, a block per head writes out and lse.
+//   finish   the combine, the accumulation, the eviction of one slot and the
+//            insert in one launch, a block per head plus one for out and lse
+//            (caches of at most 4,096 slots); longer caches take the combine,
+//            which leaves each block's smallest (score, slot), and insert.
 //
 // In cache mode the chunk's key is already in the cache: there is no column
 // M, and a slot whose token position is later than the query's (pos0) is

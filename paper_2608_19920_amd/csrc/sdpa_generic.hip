@@ -1,7 +1,8 @@
 // Generic SDPA-with-summed-weights kernels (VALU, float32 arithmetic).
 //
-// Used for float32 inputs (where the result must match float64 to ~1e-6) and
-// for bf16 shapes no faster kernel covers. Two passes over the keys of one KV
+// Used where h2o_debug_force_path(0) asks for them and for float32 calls whose
+// matrix-core kernels need more scratch than the fixed array of the calls
+// without a workspace holds. Two passes over the keys of one KV
 // head, with the row log-sum-exp computed first (Sec. "FlashAttention for
 // Summed Attention Weights": the column sums need the final row normaliser
 // lambda_r before exp(A - lambda) can be summed down a column):

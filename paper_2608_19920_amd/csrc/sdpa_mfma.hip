@@ -10,7 +10,8 @@
 //   pass B   P = exp2(S*c - lambda) on the same S; O += P V; per-wave column
 //            partials of P; O written directly (one split) or as a float32
 //            partial per split
-//   finish   column partials -> wsum (fixed order); split partials of O -> out
+//   finish   column partials -> wsum and split partials of O -> out, each in a
+//            fixed order, in one launch
 //
 // Matrix products use v_mfma_f32_16x16x32_bf16 in the S^T = K Q^T
 // orientation. For a 16(key) x 16(query) block the accumulator lane l holds
