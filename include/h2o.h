@@ -205,18 +205,20 @@ int h2o_chunk_step(const void* q, void* k_cache, void* v_cache, float* scores,
 
 /* h2o_chunk_step without a workspace argument, for callers that cannot
  * allocate device memory (code under HIP graph capture, tight serving loops,
- * harnesses that forbid allocation). Arguments, results and errors are those
- * of h2o_chunk_step (same kernels, same bits), with the scratch taken from a
- * fixed array of h2o_noalloc_scratch_bytes() bytes (32 MiB) inside the
- * library instead: one array per GPU the library runs on, held until the
- * process ends. No call allocates or frees memory. A shape whose
- * h2o_workspace_bytes() exceeds the array runs a plan that needs less (fewer
- * splits, the generic kernels for float32; its sums round differently), and
- * returns H2O_EWORKSPACE before anything is enqueued when none fits (the decode shape B8 Hq32 Hkv8 d64 M4096 needs about
- * 8 MiB). Every call on one GPU shares that GPU's array, and the array keeps
- * what the last call left there (no kernel reads it before writing it), so
- * calls that can overlap on one GPU - different streams, host threads -
- * race and must be ordered by the caller. */
+ * harnesses that forbid allocation). Arguments and errors are those of
+ * h2o_chunk_step, with the scratch taken from a fixed array of
+ * h2o_noalloc_scratch_bytes() bytes (32 MiB) inside the library instead: one
+ * array per GPU the library runs on, held until the process ends. No call
+ * allocates or frees memory. A shape whose h2o_workspace_bytes() fits the
+ * array runs the kernels of h2o_chunk_step, with the same bits (the decode
+ * shape B8 Hq32 Hkv8 d64 M4096 needs about 8 MiB). A larger one runs the
+ * fastest plan that fits, which is slower and adds its float32 sums in other
+ * groups: fewer key splits; for T == 1 the prefill kernels; for float32 larger
+ * row blocks, then the generic kernels. When none fits the call returns
+ * H2O_EWORKSPACE before anything is enqueued. Every call on one GPU shares
+ * that GPU's array, and the array keeps what the last call left there (no
+ * kernel reads it before writing it), so calls that can overlap on one GPU -
+ * different streams, host threads - race and must be ordered by the caller. */
 size_t h2o_noalloc_scratch_bytes(void);
 int h2o_chunk_step_noalloc(const void* q, void* k_cache, void* v_cache, float* scores,
                            int32_t* token_pos, const void* k_new, const void* v_new, void* out,

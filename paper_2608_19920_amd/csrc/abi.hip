@@ -145,21 +145,34 @@ int device_cus() {
 
 namespace {
 
-// The plan of one kernel path for the shape; lean: the prefill kernels without
-// key splits (the least workspace).
-Plan path_plan(const Shape& s, int path, bool lean = false) {
+// Offsets and size of the prefill paths' workspace, from the plan's splits and
+// column-partial counts.
+void layout(const Shape& s, Plan& p) {
+  const size_t BH = s.BH(), R = s.R();
+  size_t off = 0;
+  p.off_stats = off;
+  off = align256(off + (size_t)(p.nsplit_lse > p.nsplit ? p.nsplit_lse : p.nsplit) * BH * R *
+                           sizeof(float) * 2);
+  p.off_parts = off;
+  off = align256(off + (size_t)p.nparts * BH * p.parts_ld * sizeof(float));
+  p.off_opart = off;
+  if (p.nsplit > 1) off = align256(off + (size_t)p.nsplit * BH * R * s.d * sizeof(float));
+  p.off_logits = off;
+  p.off_keys = off;
+  off = align256(off + BH * (size_t)s.M * sizeof(float));
+  p.bytes = off;
+}
+
+// The plan of one kernel path for the shape: of the plans whose workspace fits
+// max_bytes the one of least time, or the smallest where none does.
+Plan path_plan(const Shape& s, int path, size_t max_bytes = SIZE_MAX) {
   Plan p{};
   const size_t BH = s.BH(), R = s.R(), Nk = s.Nk();
   p.path = path;
   p.nsplit = 1;
   p.nsplit_lse = 1;
   p.parts_ld = (int)Nk;
-  if (path == 1 && lean) {
-    p.main_waves = p.lse_waves = s.d == 128 ? 8 : 4;
-    p.rows_per_part = p.main_waves * mfma_rows_per_wave();
-    p.nparts = (int)((R + p.rows_per_part - 1) / p.rows_per_part);
-    p.parts_ld = (int)((Nk + 31) / 32 * 32);
-  } else if (path == 1) {
+  if (path == 1) {
     // Split the key range of each row tile when there are too few blocks to
     // fill the CUs (a round: the blocks resident at once). At least 8 key
     // tiles per split, at most 8 splits.
@@ -170,6 +183,38 @@ Plan path_plan(const Shape& s, int path, bool lean = false) {
       if (ns > ntiles / 8) ns = ntiles / 8;
       if (ns > maxs) ns = maxs;
       return (int)(ns < 1 ? 1 : ns);
+    };
+    // The lse pass: one round of 4-wave blocks (1,024 on 256 CUs), or of
+    // 8-wave blocks where those fill whole rounds (long cache: the pass 580
+    // against 610 us). A grid that would be one to three partly filled rounds
+    // is cut into at least three (B2 Hkv4 G7 d128 M16384 T2048: 647 us at 1.75
+    // rounds, 618 at 3.5).
+    int nl = 1, nl_round = 1;   // splits taken; of one round
+    auto lse_grid = [&](int waves, int target) {
+      const long long rows_w = (long long)waves * mfma_rows_per_wave();
+      const long long nb = (((long long)R + rows_w - 1) / rows_w) * (long long)BH;
+      nl = nl_round = pick(nb, target, kMaxLseSplit);
+      if (nb * nl % target != 0 && nb * nl > target && nb * nl < 3 * target &&
+          ntiles * nb >= 96ll * target)
+        nl = pick(nb, 3 * target, kMaxLseSplit);
+      return nb * nl % (cus * (16 / waves)) == 0;
+    };
+    p.lse_waves = s.d == 128 && lse_grid(8, (int)(2 * cus)) ? 8 : 4;
+    if (p.lse_waves == 4) lse_grid(4, (int)(4 * cus));
+    p.parts_ld = (int)((Nk + 31) / 32 * 32);
+    // The plan with n splits of a main pass of `waves` waves a block. Where it
+    // does not fit, the lse pass gives up splits down to nl_min (8 bytes a row
+    // each, against 4 d of a main-pass split).
+    auto with_main = [&](int waves, int n, int nl_min) {
+      Plan c = p;
+      c.main_waves = waves;
+      c.nsplit = n;
+      c.rows_per_part = waves * mfma_rows_per_wave();
+      c.nparts = (int)((R + c.rows_per_part - 1) / c.rows_per_part);
+      for (c.nsplit_lse = nl;; --c.nsplit_lse) {
+        layout(s, c);
+        if (c.bytes <= max_bytes || c.nsplit_lse <= nl_min) return c;
+      }
     };
     // The main pass: the block shape (4 waves, or 8 at d = 128) and split of
     // least estimated time. us[k-1]: microseconds per key tile of a block
@@ -189,13 +234,13 @@ Plan path_plan(const Shape& s, int path, bool lean = false) {
     static const Shape4 kD128[] = {{8, 1, {0.96, 0, 0}}, {4, 2, {0.58, 1.07, 0}}};
     static const Shape4 kD64[] = {{4, 3, {0.39, 0.62, 0.91}}};
     const int nshapes = s.d == 128 ? 2 : 1;
-    long long nrt = 0;
+    Plan sel = with_main(s.d == 128 ? 8 : 4, 1, 1);   // the smallest
     int ns = 0;
     double best = 0;
     for (int v = 0; v < nshapes; ++v) {
       const Shape4& b = s.d == 128 ? kD128[v] : kD64[v];
       const long long rows_w = (long long)b.waves * mfma_rows_per_wave();
-      const long long nrt_v = ((long long)R + rows_w - 1) / rows_w, nb = nrt_v * (long long)BH;
+      const long long nb = ((long long)R + rows_w - 1) / rows_w * (long long)BH;
       for (int n = 1; n <= 8 && (n == 1 || n <= ntiles / 8); ++n) {
         const long long blocks = nb * n, round = cus * b.resident;
         const long long full = blocks / round, left = (blocks % round + cus - 1) / cus;
@@ -205,34 +250,15 @@ Plan path_plan(const Shape& s, int path, bool lean = false) {
         if (n > 1) us += 2.0 + (double)n * (double)BH * (double)R * s.d * 4.0 / 3.0e6;
         // a clear gain is asked of more splits (their partials take memory)
         if (ns == 0 || us < 0.97 * best) {
+          const Plan c = with_main(b.waves, n, nl_round);
+          if (c.bytes > max_bytes) continue;
           best = us;
           ns = n;
-          nrt = nrt_v;
-          p.main_waves = b.waves;
+          sel = c;
         }
       }
     }
-    p.nsplit = ns;
-    // The lse pass: one round of 4-wave blocks (1,024 on 256 CUs), or of
-    // 8-wave blocks where those fill whole rounds (long cache: the pass 580
-    // against 610 us). A grid that would be one to three partly filled rounds
-    // is cut into at least three (G7 above: 647 us at 1.75 rounds, 618 at 3.5).
-    auto lse_grid = [&](int waves, int target, int& ns_w) {
-      const long long rows_w = (long long)waves * mfma_rows_per_wave();
-      const long long nb = (((long long)R + rows_w - 1) / rows_w) * (long long)BH;
-      ns_w = pick(nb, target, kMaxLseSplit);
-      if (nb * ns_w % target != 0 && nb * ns_w > target && nb * ns_w < 3 * target &&
-          ntiles * nb >= 96ll * target)
-        ns_w = pick(nb, 3 * target, kMaxLseSplit);
-      return nb * ns_w % (cus * (16 / waves)) == 0;
-    };
-    int nl = 1;
-    p.lse_waves = s.d == 128 && lse_grid(8, (int)(2 * cus), nl) ? 8 : 4;
-    if (p.lse_waves == 4) lse_grid(4, (int)(4 * cus), nl);
-    p.nsplit_lse = nl;
-    p.rows_per_part = p.main_waves * mfma_rows_per_wave();
-    p.nparts = (int)nrt;
-    p.parts_ld = (int)((Nk + 31) / 32 * 32);
+    return sel;
   } else if (path == 2) {
     p.nsplit = s.M > 0 ? decode_max_split() : 0;   // capacity; the launch picks the count
     p.rows_per_part = 0;
@@ -250,25 +276,18 @@ Plan path_plan(const Shape& s, int path, bool lean = false) {
     return p;
   } else if (path == 3) {
     // 32-row blocks read the keys half as often; 16-row blocks where 32 rows
-    // would leave CUs without a block
+    // would leave CUs without a block, if their column partials fit
     p.rows_per_part = (R + 31) / 32 * BH >= (size_t)device_cus() ? 32 : 16;
     p.nparts = (int)((R + p.rows_per_part - 1) / p.rows_per_part);
+    layout(s, p);
+    if (p.bytes <= max_bytes) return p;
+    p.rows_per_part = 32;
+    p.nparts = (int)((R + 31) / 32);
   } else {
     p.rows_per_part = 64;
     p.nparts = (int)((R + 63) / 64);
   }
-  size_t off = 0;
-  p.off_stats = off;
-  off = align256(off + (size_t)(p.nsplit_lse > p.nsplit ? p.nsplit_lse : p.nsplit) * BH * R *
-                           sizeof(float) * 2);
-  p.off_parts = off;
-  off = align256(off + (size_t)p.nparts * BH * p.parts_ld * sizeof(float));
-  p.off_opart = off;
-  if (p.nsplit > 1) off = align256(off + (size_t)p.nsplit * BH * R * s.d * sizeof(float));
-  p.off_logits = off;
-  p.off_keys = off;
-  off = align256(off + BH * (size_t)s.M * sizeof(float));
-  p.bytes = off;
+  layout(s, p);
   return p;
 }
 
@@ -277,9 +296,9 @@ Plan path_plan(const Shape& s, int path, bool lean = false) {
 Plan make_plan(const Shape& s, int dtype, size_t max_bytes) {
   const int forced = g_forced_path.load();
   if (dtype != H2O_BF16) {
-    // the generic kernels where asked for, or where the smaller blocks'
-    // column partials do not fit
-    const Plan p = path_plan(s, forced == 0 ? 0 : 3);
+    // the generic kernels where asked for, or where the matrix-core kernels'
+    // column partials (of 16 or 32 rows against 64) do not fit
+    const Plan p = path_plan(s, forced == 0 ? 0 : 3, max_bytes);
     return p.bytes <= max_bytes ? p : path_plan(s, 0);
   }
   int path = forced;
@@ -287,11 +306,9 @@ Plan make_plan(const Shape& s, int dtype, size_t max_bytes) {
   const bool decode = s.T == 1 && decode_supports(s.d, s.G());
   if (path < 0) path = decode ? 2 : 1;
   if (path == 2 && !decode) path = 1;
-  const Plan p = path_plan(s, path);
+  const Plan p = path_plan(s, path, max_bytes);
   // (the decode kernels' stored logits are the larger part of their scratch)
-  if (p.bytes <= max_bytes || path == 0) return p;
-  const Plan p1 = path == 1 ? p : path_plan(s, 1);
-  return p1.bytes <= max_bytes ? p1 : path_plan(s, 1, true);
+  return p.bytes <= max_bytes || path != 2 ? p : path_plan(s, 1, max_bytes);
 }
 
 namespace {

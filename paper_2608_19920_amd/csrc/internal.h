@@ -119,7 +119,8 @@ struct Plan {
   size_t off_keys;     // float accumulated scores [BH][M], the ranking copy of a chunk step
   size_t bytes;
 };
-// The plan of the least time whose workspace fits max_bytes, or the smallest.
+// The plan of the least time whose workspace fits max_bytes; where none fits, the
+// smallest one.
 Plan make_plan(const Shape& s, int dtype, size_t max_bytes = SIZE_MAX);
 constexpr int kMaxLseSplit = 16;  // key-range splits of the MFMA lse pass, at most
 int mfma_rows_per_wave();        // packed rows per wave of the MFMA kernels
