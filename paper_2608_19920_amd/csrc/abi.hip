@@ -221,35 +221,38 @@ Plan path_plan(const Shape& s, int path, size_t max_bytes = SIZE_MAX) {
     // that shares its CU with k - 1 others; a round takes every block's tiles
     // at full residency, the last one at what is left, and about 8 us to start
     // and end; the O partials of several splits are written, read and reduced
-    // (2 us and a byte of them in 1 / 3 TB/s).
-    // Fitted on sweeps of the split at B1 Hkv8 M8192 T1024, B4 Hkv8 M32768 T512
-    // and B2 Hkv4 G7 M16384 T2048 (d = 128), B5 Hkv16 M15102 T433 and B3 Hkv16
-    // M3001 T333 (d = 64): within 10 % of the measured passes (e.g. G7, 8 waves
-    // in 1, 2, 4 splits: 1,060, 1,076, 973 estimated, 1,048, 1,068, 978 measured;
-    // d = 64, T433 in 1, 2, 4: 311, 231, 207 and 320, 236, 207). A rule that only
-    // filled one round took 4 waves in two splits at G7 (1,039 us and 22 of
-    // reducing) and two splits at T433 (236), seven at B1 Hkv8 d128 M2000 T300
-    // (31 us, 22 in three).
+    // (2 us and a byte of them in 1 / 3 TB/s). Cache mode has its own figures at
+    // d = 128 (the position mask; every row tile takes every key tile).
+    // Against the pass and its reduces measured in every shape and split (1,550
+    // random shapes of B 1-8, 4 to 16 KV heads, M 256-32768, T 2-2048) the estimate is
+    // off by 9 % (rms) at d = 128 and 18 % at d = 64, and the plan taken is 0.7 % and
+    // 2.9 % slower than the best one (geometric mean). What decides between 4 waves
+    // and 8 in more splits is the time of a 4-wave block alone on its CU: at 0.58 in
+    // both modes, 4 unsplit waves would be taken at B1 Hkv8 G4 M1990 T695 (66 us; 54
+    // with 8 waves in two splits) and at B1 Hkv4 G8 M3412 T739 in cache mode (97; 71).
     struct Shape4 { int waves, resident; double us[3]; };
-    static const Shape4 kD128[] = {{8, 1, {0.96, 0, 0}}, {4, 2, {0.58, 1.07, 0}}};
+    static const Shape4 kD128[] = {{8, 1, {0.96, 0, 0}}, {4, 2, {0.65, 1.0, 0}}};
+    static const Shape4 kCache128[] = {{8, 1, {1.0, 0, 0}}, {4, 2, {0.80, 1.07, 0}}};
     static const Shape4 kD64[] = {{4, 3, {0.39, 0.62, 0.91}}};
+    const Shape4* shapes = s.d == 64 ? kD64 : s.cache_only ? kCache128 : kD128;
     const int nshapes = s.d == 128 ? 2 : 1;
     Plan sel = with_main(s.d == 128 ? 8 : 4, 1, 1);   // the smallest
     int ns = 0;
-    double best = 0;
-    for (int v = 0; v < nshapes; ++v) {
-      const Shape4& b = s.d == 128 ? kD128[v] : kD64[v];
-      const long long rows_w = (long long)b.waves * mfma_rows_per_wave();
-      const long long nb = ((long long)R + rows_w - 1) / rows_w * (long long)BH;
-      for (int n = 1; n <= 8 && (n == 1 || n <= ntiles / 8); ++n) {
+    double best = INFINITY;
+    for (int n = 1; n <= 8 && (n == 1 || n <= ntiles / 8); ++n)
+      for (int v = 0; v < nshapes; ++v) {
+        const Shape4& b = shapes[v];
+        const long long rows_w = (long long)b.waves * mfma_rows_per_wave();
+        const long long nb = ((long long)R + rows_w - 1) / rows_w * (long long)BH;
         const long long blocks = nb * n, round = cus * b.resident;
         const long long full = blocks / round, left = (blocks % round + cus - 1) / cus;
         const double tiles = (double)((ntiles + n - 1) / n);
         double us = tiles * (full * b.us[b.resident - 1] + (left ? b.us[left - 1] : 0.0)) +
                     8.0 * (double)(full + (left != 0));
         if (n > 1) us += 2.0 + (double)n * (double)BH * (double)R * s.d * 4.0 / 3.0e6;
-        // a clear gain is asked of more splits (their partials take memory)
-        if (ns == 0 || us < 0.97 * best) {
+        // a clear gain is asked of more splits (their partials take memory), not
+        // of the other block shape at as many
+        if (us < (n > ns ? 0.97 : 1.0) * best) {
           const Plan c = with_main(b.waves, n, nl_round);
           if (c.bytes > max_bytes) continue;
           best = us;
@@ -257,7 +260,6 @@ Plan path_plan(const Shape& s, int path, size_t max_bytes = SIZE_MAX) {
           sel = c;
         }
       }
-    }
     return sel;
   } else if (path == 2) {
     p.nsplit = s.M > 0 ? decode_max_split() : 0;   // capacity; the launch picks the count
