@@ -47,6 +47,10 @@
  *    touched. h2o_last_error() returns a message for the calling thread's
  *    last non-OK status.
  *  - Calls that share buffers must be ordered by the caller (same stream).
+ *  - A query and a key that do not see each other contribute 0 to every result.
+ *    In float32 that holds whatever the values are. In bfloat16 the values must
+ *    be finite: the matrix products take an invisible pair with weight 0, and an
+ *    Inf or NaN in its value row or output gradient can reach the rows near it.
  */
 #ifndef H2O_H
 #define H2O_H

@@ -71,10 +71,11 @@ struct RowPos {
     g += ng;
     if (g >= a.G) { g -= a.G; ++i; }
   }
-  // its row of [B, Hq, T, .] (row 0 of the head where it lies past R)
-  __device__ __forceinline__ size_t index(const Args& a, int b, int h) const {
+  // its row of the group's [G, T, .] (row 0 where it lies past R); the group's
+  // floats are fewer than 2^30 a head, their bytes a 32-bit offset
+  __device__ __forceinline__ uint32_t index(const Args& a) const {
     const bool ok = r < a.R;
-    return (size_t)(b * a.Hq + h * a.G + (ok ? g : 0)) * a.T + (ok ? i : 0);
+    return (uint32_t)((ok ? g : 0) * a.T + (ok ? i : 0));
   }
 };
 // Earliest chunk position that sees key j (T: none).
@@ -156,6 +157,54 @@ __device__ __forceinline__ void zero(f32x4 (&acc)[D / 64][4]) {
   for (int h = 0; h < D / 64; ++h)
 #pragma unroll
     for (int u = 0; u < 4; ++u) acc[h][u] = f32x4{0.f, 0.f, 0.f, 0.f};
+}
+
+// A product takes all 16 streamed rows for all 16 LDS rows: a pair that does not
+// see each other enters it with weight 0, and 0 times an Inf or NaN is NaN. A
+// wave whose sums are not all finite after its loop takes them again with
+// add_seen_rows, which leaves such pairs out. Tested inside the loop it took 24
+// registers and a block per CU; behind it, B1 Hq16 Hkv4 d64 M2048 T256 takes 59.7,
+// 56.7 and 75.8 us (attention, dq, dk/dv) against 58.9, 56.3 and 74.9 without.
+// What the second loop is computed from goes through opaque(), so that nothing
+// of it is shared with, or kept in registers across, the first.
+__device__ __forceinline__ int opaque(int x) {
+  asm volatile("" : "+v"(x));
+  return x;
+}
+// nan_if_nonfinite: 0, or NaN where an element is Inf or NaN.
+template <int D>
+__device__ __forceinline__ float nan_if_nonfinite(const f32x4 (&acc)[D / 64][4]) {
+  float z = 0.f;
+#pragma unroll
+  for (int h = 0; h < D / 64; ++h)
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) z = fmaf(acc[h][u][r], 0.f, z);
+  return z;
+}
+// add_rows over the pairs that see each other: the streamed rows one by one, row(k)
+// their address. hidden: bit r set where this lane's pair of row 4 g4 + r is hidden.
+template <int D, class Row>
+__device__ __forceinline__ void add_seen_rows(f32x4 (&acc)[D / 64][4], const f32x4& w, int hidden,
+                                              int l16, int g4, Row&& row) {
+#pragma unroll 1
+  for (int k = 0; k < kStep; ++k) {
+    const int from = 16 * (k >> 2) + l16, r = k & 3;
+    const float wr = r == 0 ? w[0] : r == 1 ? w[1] : r == 2 ? w[2] : w[3];
+    const float p = __shfl(wr, from, 64);
+    const bool seen = !((__shfl(hidden, from, 64) >> r) & 1);
+    const float* src = row(k) + 16 * g4;
+#pragma unroll
+    for (int h = 0; h < D / 64; ++h)
+#pragma unroll
+      for (int c = 0; c < 4; ++c) {
+        const f32x4 x = load4(src + 64 * h + 4 * c);
+#pragma unroll
+        for (int u = 0; u < 4; ++u) acc[h][u][c] = seen ? fmaf(p, x[u], acc[h][u][c]) : acc[h][u][c];
+        __builtin_amdgcn_sched_barrier(0);   // few registers: the path is rare
+      }
+  }
 }
 
 // acc of all waves added into wave 0's, in a fixed tree order, through LDS of
@@ -342,6 +391,32 @@ __global__ __launch_bounds__(NW * 64) void f32_attend(Args a, float* __restrict_
     if (l16 < 4 && j < kv_end)
       prow[j] = l16 == 0 ? cs[0] : l16 == 1 ? cs[1] : l16 == 2 ? cs[2] : cs[3];
   }
+  float z = 0.f;
+#pragma unroll
+  for (int n = 0; n < NQB; ++n) z += nan_if_nonfinite<D>(o[n]);
+  if (__builtin_expect(__builtin_amdgcn_ballot_w64(z != 0.f) != 0, 0)) {   // wave-uniform
+    const int wv = __builtin_amdgcn_readfirstlane(opaque(wave)), li = opaque(l16), gi = opaque(g4);
+#pragma unroll
+    for (int n = 0; n < NQB; ++n) zero<D>(o[n]);
+#pragma unroll 1
+    for (int s = wv; s < nsteps; s += NW) {
+      f32x4 k[D / 16], sc[NQB];
+      load_pieces<D>(k, key_row(a.kc, a.kn, a, bh, min(s * kStep + li, kv_end - 1), D), gi);
+      dot_rows<D, NQB>(sc, k, Qs, li, gi);
+#pragma unroll
+      for (int n = 0; n < NQB; ++n) {
+        int hidden = 0;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          hidden |= (int)(key_rel<CACHE>(a, bh, s * kStep + 4 * gi + r) > qi[n]) << r;
+          sc[n][r] = expf(sc[n][r] - lam[n]);
+        }
+        add_seen_rows<D>(o[n], sc[n], hidden, li, gi, [&](int i) {
+          return key_row(a.vc, a.vn, a, bh, min(s * kStep + i, kv_end - 1), D);
+        });
+      }
+    }
+  }
   reduce_waves<D, NQB, NW>(o, red, wave, l16, g4);
   if (wave == 0) {
 #pragma unroll
@@ -355,11 +430,13 @@ __global__ __launch_bounds__(NW * 64) void f32_attend(Args a, float* __restrict_
 // ----------------------------------------------------------------- backward
 // dQ_r = scale (sum_j P dP K_j - D_r sum_j P K_j) and D_r = sum_j P dP from
 // one sweep over the keys, 16 packed rows per block.
+// At d = 128 a block of 8 waves is alone on its CU: told so (two waves per SIMD),
+// and with the masks behind the products, the compiler keeps more loads in
+// flight (B1 Hq16 Hkv4 M2048 T256 121 -> 110 us).
 template <int D, bool CACHE, int NW>
-__global__ __launch_bounds__(NW * 64) void f32_bwd_dq(Args a, const float* __restrict__ dout,
-                                                  const float* __restrict__ lse,
-                                                  float* __restrict__ dq,
-                                                  float* __restrict__ dot) {
+__global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2, D == 64 ? 8 : 2)))
+void f32_bwd_dq(Args a, const float* __restrict__ dout, const float* __restrict__ lse,
+                float* __restrict__ dq, float* __restrict__ dot) {
   constexpr int P = pitch<D>();
   __shared__ __attribute__((aligned(16))) float Qs[16 * P], Os[16 * P];
   __shared__ __attribute__((aligned(16))) float red[NW / 2 * 16 * P];
@@ -387,12 +464,12 @@ __global__ __launch_bounds__(NW * 64) void f32_bwd_dq(Args a, const float* __res
     const int jr = min(s * kStep + l16, kv_end - 1);
     load_pieces<D>(k, key_row(a.kc, a.kn, a, bh, jr, D), g4);
     load_pieces<D>(v, key_row(a.vc, a.vn, a, bh, jr, D), g4);
-    int rel[4];
-#pragma unroll
-    for (int u = 0; u < 4; ++u) rel[u] = key_rel<CACHE>(a, bh, s * kStep + 4 * g4 + u);
     f32x4 sc[1], dp[1];
     dot_rows<D, 1>(sc, k, Qs, l16, g4);
     dot_rows<D, 1>(dp, v, Os, l16, g4);
+    int rel[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) rel[u] = key_rel<CACHE>(a, bh, s * kStep + 4 * g4 + u);
     // the second read of k goes out once the first is used (registers)
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
@@ -411,6 +488,34 @@ __global__ __launch_bounds__(NW * 64) void f32_bwd_dq(Args a, const float* __res
     }
     add_rows<D>(ad[0], kt, dp[0]);
     add_rows<D>(ap, kt, sc[0]);
+  }
+  const float z = nan_if_nonfinite<D>(ad[0]) + nan_if_nonfinite<D>(ap) + dsum * 0.f;
+  if (__builtin_expect(__builtin_amdgcn_ballot_w64(z != 0.f) != 0, 0)) {   // wave-uniform
+    const int wv = __builtin_amdgcn_readfirstlane(opaque(wave)), li = opaque(l16), gi = opaque(g4);
+    zero<D>(ad[0]);
+    zero<D>(ap);
+    dsum = 0.f;
+#pragma unroll 1
+    for (int s = wv; s < nsteps; s += NW) {
+      auto key = [&](int k) { return min(s * kStep + k, kv_end - 1); };
+      f32x4 v[D / 16], sc[1], dp[1];
+      load_pieces<D>(v, key_row(a.kc, a.kn, a, bh, key(li), D), gi);
+      dot_rows<D, 1>(sc, v, Qs, li, gi);
+      load_pieces<D>(v, key_row(a.vc, a.vn, a, bh, key(li), D), gi);
+      dot_rows<D, 1>(dp, v, Os, li, gi);
+      int hidden = 0;
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const bool hid = key_rel<CACHE>(a, bh, s * kStep + 4 * gi + u) > qi;
+        hidden |= (int)hid << u;
+        sc[0][u] = expf(sc[0][u] * a.scale - lam);
+        dp[0][u] *= sc[0][u];
+        if (!hid) dsum += dp[0][u];
+      }
+      auto row = [&](int k) { return key_row(a.kc, a.kn, a, bh, key(k), D); };
+      add_seen_rows<D>(ad[0], dp[0], hidden, li, gi, row);
+      add_seen_rows<D>(ap, sc[0], hidden, li, gi, row);
+    }
   }
   dsum += __shfl_xor(dsum, 16, 64);
   dsum += __shfl_xor(dsum, 32, 64);
@@ -431,16 +536,15 @@ __global__ __launch_bounds__(NW * 64) void f32_bwd_dq(Args a, const float* __res
 }
 
 // dV_j = sum_r P_rj dout_r and dK_j = scale sum_r P (dP - D_r) Q_r over the
-// head's packed rows, 16 keys per block.
+// head's packed rows, 16 keys per block. 128 registers at d = 64 (two blocks per CU);
+// the group's rows are addressed by 32-bit offsets, which keeps the kernels free
+// of spills.
 template <int D, bool CACHE, int NW>
-__global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(D == 64 ? 4 : 1)))
-void f32_bwd_dkdv(Args a, const float* __restrict__ dout,
-                                                    const float* __restrict__ lse,
-                                                    const float* __restrict__ dot,
-                                                    float* __restrict__ dkc,
-                                                    float* __restrict__ dvc,
-                                                    float* __restrict__ dkn,
-                                                    float* __restrict__ dvn) {
+__global__ __launch_bounds__(NW * 64)
+__attribute__((amdgpu_waves_per_eu(D == 64 ? 4 : 2, D == 64 ? 4 : 8)))
+void f32_bwd_dkdv(Args a, const float* __restrict__ dout, const float* __restrict__ lse,
+                  const float* __restrict__ dot, float* __restrict__ dkc,
+                  float* __restrict__ dvc, float* __restrict__ dkn, float* __restrict__ dvn) {
   constexpr int P = pitch<D>();
   __shared__ __attribute__((aligned(16))) float Ks[16 * P], Vs[16 * P];
   __shared__ __attribute__((aligned(16))) float red[NW / 2 * 16 * P];
@@ -467,26 +571,32 @@ void f32_bwd_dkdv(Args a, const float* __restrict__ dout,
   zero<D>(dv[0]);
   constexpr int kAdv = kStep * NW;
   const int ni = kAdv / a.G, ng = kAdv % a.G;
+  const size_t group = (size_t)(b * a.Hq + h * a.G) * a.T;
+  const float *qh = a.q + group * D, *dh = dout + group * D, *lh = lse + group;
+  auto at = [](const float* base, uint32_t bytes) {
+    return reinterpret_cast<const float*>(reinterpret_cast<const char*>(base) + bytes);
+  };
   RowPos pa(a, (s0 + wave) * kStep + l16), pb(a, (s0 + wave) * kStep + 4 * g4);
   for (int s = s0 + wave; s < s1; s += NW) {
     f32x4 q[D / 16], od[D / 16], qt[D / 64][4], ot[D / 64][4];
-    const size_t ra = pa.index(a, b, h) * D;
-    load_pieces<D>(q, a.q + ra, g4);
-    load_pieces<D>(od, dout + ra, g4);
+    const uint32_t ra = pa.index(a) * (uint32_t)(D * 4);
+    load_pieces<D>(q, at(qh, ra), g4);
+    load_pieces<D>(od, at(dh, ra), g4);
     float lam[4], dr[4];
     int pos[4];
-    size_t row[4];
+    uint32_t row[4];   // bytes
     RowPos pu = pb;
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
       const bool ok = pu.r < a.R;
-      row[u] = pu.index(a, b, h);
-      lam[u] = lse[row[u]];
+      const uint32_t ri = pu.index(a);
+      row[u] = ri * (uint32_t)(D * 4) + 16u * l16;
+      lam[u] = *at(lh, ri * 4u);
       dr[u] = dot[bh * a.R + (ok ? pu.r : 0)];
       pos[u] = ok && lam[u] > -INFINITY ? pu.i : INT32_MIN;   // none visible
 #pragma unroll
       for (int hh = 0; hh < D / 64; ++hh)
-        ot[hh][u] = load4(dout + row[u] * D + 4 * l16 + 64 * hh);
+        ot[hh][u] = load4(at(dh, row[u] + 256u * hh));
       pu.advance(a, 1, 0, 1);
     }
     pa.advance(a, kAdv, ni, ng);
@@ -500,7 +610,7 @@ void f32_bwd_dkdv(Args a, const float* __restrict__ dout,
     for (int u = 0; u < 4; ++u)
 #pragma unroll
       for (int hh = 0; hh < D / 64; ++hh)
-        qt[hh][u] = load4(a.q + row[u] * D + 4 * l16 + 64 * hh);
+        qt[hh][u] = load4(at(qh, row[u] + 256u * hh));
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
       const float p = rel > pos[u] ? 0.f : expf(sc[0][u] * a.scale - lam[u]);
@@ -510,11 +620,44 @@ void f32_bwd_dkdv(Args a, const float* __restrict__ dout,
     add_rows<D>(dv[0], ot, sc[0]);
     add_rows<D>(dk[0], qt, dp[0]);
   }
+  const float z = nan_if_nonfinite<D>(dk[0]) + nan_if_nonfinite<D>(dv[0]);
+  if (__builtin_expect(__builtin_amdgcn_ballot_w64(z != 0.f) != 0, 0)) {   // wave-uniform
+    const int wv = __builtin_amdgcn_readfirstlane(opaque(wave)), li = opaque(l16), gi = opaque(g4);
+    zero<D>(dk[0]);
+    zero<D>(dv[0]);
+#pragma unroll 1
+    for (int s = s0 + wv; s < s1; s += NW) {
+      // packed row s kStep + k as a row of [B, Hq, T, .] (row 0 where it lies past R)
+      auto packed = [&](int k) { return s * kStep + k < a.R ? s * kStep + k : 0; };
+      f32x4 v[D / 16], sc[1], dp[1];
+      load_pieces<D>(v, a.q + row_index(a, b, h, packed(li)) * D, gi);
+      dot_rows<D, 1>(sc, v, Ks, li, gi);
+      load_pieces<D>(v, dout + row_index(a, b, h, packed(li)) * D, gi);
+      dot_rows<D, 1>(dp, v, Vs, li, gi);
+      int hidden = 0;
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const int r = packed(4 * gi + u);
+        const float lam = lse[row_index(a, b, h, r)];
+        const bool hid = s * kStep + 4 * gi + u >= a.R || !(lam > -INFINITY) || rel > r / a.G;
+        hidden |= (int)hid << u;
+        sc[0][u] = expf(sc[0][u] * a.scale - lam);
+        dp[0][u] = sc[0][u] * (dp[0][u] - dot[bh * a.R + r]);
+      }
+      add_seen_rows<D>(dv[0], sc[0], hidden, li, gi, [&](int k) {
+        return dout + row_index(a, b, h, packed(k)) * D;
+      });
+      add_seen_rows<D>(dk[0], dp[0], hidden, li, gi, [&](int k) {
+        return a.q + row_index(a, b, h, packed(k)) * D;
+      });
+    }
+  }
   reduce_waves<D, 1, NW>(dk, red, wave, l16, g4);
   reduce_waves<D, 1, NW>(dv, red, wave, l16, g4);
-  if (wave == 0 && j < a.Nk) {
-    const bool cached = j < a.M;
-    const size_t o = (cached ? bh * a.M + j : bh * a.T + (j - a.M)) * (size_t)D;
+  const int jo = j0 + opaque(l16);   // j, not kept through the loop
+  if (wave == 0 && jo < a.Nk) {
+    const bool cached = jo < a.M;
+    const size_t o = (cached ? bh * a.M + jo : bh * a.T + (jo - a.M)) * (size_t)D;
     store_row<D>((cached ? dkc : dkn) + o, dk[0], g4, a.scale);
     store_row<D>((cached ? dvc : dvn) + o, dv[0], g4, 1.f);
   }
