@@ -789,19 +789,19 @@ __global__ __launch_bounds__(64) void decode_insert(
 // (lower slot first among equal scores; -0 equals +0), and the insert of the
 // chunk's key, value, score wsum[M] and token position into that slot. Same
 // arithmetic as the combine, accumulate and argmin-insert kernels. The block
-// is latency-bound on 64 or so CUs: everything it reads (the logits and
-// scores of the first pass of slots, 16 bytes per load, the split
-// statistics, the query and the chunk's key and value rows) is requested
-// before the first value is used; slot groups past the cache do no
-// arithmetic; and of the last pass (the only pass at the decode shapes) the
-// summed weights are stored before the block's argmin, the scores only after
-// the slot is chosen, so that the chosen slot's score is written once, with
-// its new value. out and lse come from a second block per head, on a CU of
-// its own (in the first block they stood between the statistics and the
-// slots: B8 Hkv8 G4 d64 M4096 18.2 -> 17.5 us a step, B1 Hkv8 d128 13.2 -> 11.8).
+// is latency-bound on 64 or so CUs: it takes its slots in one pass (M <=
+// kFinSlots); everything it reads (the logits and scores of its slots, 16
+// bytes per load, the split statistics, the query and the chunk's key and
+// value rows) is requested before the first value is used; slot groups past
+// the cache do no arithmetic; and the summed weights are stored before the
+// block's argmin, the scores only after the slot is chosen, so that the
+// chosen slot's score is written once, with its new value. out and lse come
+// from a second block per head, on a CU of its own (in the first block they
+// stood between the statistics and the slots: B8 Hkv8 G4 d64 M4096 18.2 -> 17.5
+// us a step, B1 Hkv8 d128 13.2 -> 11.8).
 constexpr int kFinThreads = 1024;
-constexpr int kFinVec = 4;                          // consecutive slots per thread and pass
-constexpr int kFinPass = kFinThreads * kFinVec;     // slots per pass
+constexpr int kFinVec = 4;                          // consecutive slots per thread
+constexpr int kFinSlots = kFinThreads * kFinVec;    // slots of a head, at most
 
 // Blocks x < heads do the slots of head x, blocks heads + x its out and lse;
 // with OUT false (the eviction half of a step, whose attend call wrote out and
@@ -845,24 +845,11 @@ __global__ __launch_bounds__(kFinThreads) void decode_finish(
   float* sc = scores + bh * (size_t)M;
   const float* lgb = logits + bh * (size_t)G * pitch;
   const bool sc16 = (M & 3) == 0;     // score rows start 16-byte aligned
-  // This thread's slots of a pass are j0 .. j0 + 3, j0 = base + 4 * tid. A
-  // logit row is padded to a multiple of 4 slots, so a group that starts in
-  // the cache is read whole; its slots past the cache are not used.
+  // This thread's slots are j0 .. j0 + 3. A logit row is padded to a multiple
+  // of 4 slots, so a group that starts in the cache is read whole; its slots
+  // past the cache are not used.
+  const int j0 = kFinVec * tid;
   f32x4 lg[G], sv;
-  auto load_pass = [&](int base) {
-    const int j0 = base + kFinVec * tid;
-    if (j0 < M) {
-#pragma unroll
-      for (int g = 0; g < G; ++g)
-        lg[g] = *reinterpret_cast<const f32x4*>(lgb + (size_t)g * pitch + j0);
-      if (sc16) {
-        sv = *reinterpret_cast<const f32x4*>(sc + j0);
-      } else {
-#pragma unroll
-        for (int r = 0; r < kFinVec; ++r) sv[r] = sc[min(j0 + r, M - 1)];
-      }
-    }
-  };
   typedef uint32_t u4 __attribute__((ext_vector_type(4)));
   u4 krow = {0u, 0u, 0u, 0u}, vrow = {0u, 0u, 0u, 0u};
   if (tid < D / 8) {
@@ -871,43 +858,38 @@ __global__ __launch_bounds__(kFinThreads) void decode_finish(
   }
   StatsIn<D, G, NT> sin;
   sin.load(q, kn, dstat, Hq, Hkv, nsplit, bh, true);
-  load_pass(0);
-  sin.finish(hs, Hq, Hkv, nsplit, c_log2, bh, nullptr, true);
-  // Passes in increasing slot order; a thread visits its slots in
-  // increasing order, so a strict < keeps the lowest slot among equal keys.
-  // The start (max key, slot 0) is a real pair whenever every key is the
-  // maximum, so the choice is always a slot of the cache.
-  uint32_t bk = 0xFFFFFFFFu, bj = 0u;
-  f32x4 wv, sa;
-  int base = 0;
-  for (;;) {
-    const int j0 = base + kFinVec * tid;
-    if (j0 < M) {
+  if (j0 < M) {
 #pragma unroll
-      for (int r = 0; r < kFinVec; ++r) {
-        float wj = 0.f;
+    for (int g = 0; g < G; ++g)
+      lg[g] = *reinterpret_cast<const f32x4*>(lgb + (size_t)g * pitch + j0);
+    if (sc16) {
+      sv = *reinterpret_cast<const f32x4*>(sc + j0);
+    } else {
 #pragma unroll
-        for (int g = 0; g < G; ++g) wj += __builtin_amdgcn_exp2f(lg[g][r] - hs.lam[g]);
-        wv[r] = wj;
-        sa[r] = sv[r] + wj;
-        const uint32_t key = order_key(sa[r]);
-        if (j0 + r < M && key < bk) { bk = key; bj = (uint32_t)(j0 + r); }
-      }
+      for (int r = 0; r < kFinVec; ++r) sv[r] = sc[min(j0 + r, M - 1)];
     }
-    if (base + kFinPass >= M) break;   // the last pass is stored after the choice
-#pragma unroll
-    for (int r = 0; r < kFinVec; ++r)
-      if (j0 + r < M) {
-        w[j0 + r] = wv[r];
-        sc[j0 + r] = sa[r];
-      }
-    base += kFinPass;
-    load_pass(base);
   }
-  {
-    // the last pass's summed weights do not wait for the choice: stored
-    // before the block's argmin, they drain while it runs
-    const int j0 = base + kFinVec * tid;
+  sin.finish(hs, Hq, Hkv, nsplit, c_log2, bh, nullptr, true);
+  // A thread visits its slots in increasing order, so a strict < keeps the
+  // lowest slot among equal keys. The start (max key, slot 0) is a real pair
+  // whenever every key is the maximum, so the choice is always a slot of the
+  // cache.
+  uint32_t bk = 0xFFFFFFFFu, bj = 0u;
+  f32x4 sa;
+  if (j0 < M) {
+    f32x4 wv;
+#pragma unroll
+    for (int r = 0; r < kFinVec; ++r) {
+      float wj = 0.f;
+#pragma unroll
+      for (int g = 0; g < G; ++g) wj += __builtin_amdgcn_exp2f(lg[g][r] - hs.lam[g]);
+      wv[r] = wj;
+      sa[r] = sv[r] + wj;
+      const uint32_t key = order_key(sa[r]);
+      if (j0 + r < M && key < bk) { bk = key; bj = (uint32_t)(j0 + r); }
+    }
+    // the summed weights do not wait for the choice: stored before the block's
+    // argmin, they drain while it runs
 #pragma unroll
     for (int r = 0; r < kFinVec; ++r)
       if (j0 + r < M) w[j0 + r] = wv[r];
@@ -922,25 +904,15 @@ __global__ __launch_bounds__(kFinThreads) void decode_finish(
     if (lex_less(red_k[v], red_j[v], bk, bj)) { bk = red_k[v]; bj = red_j[v]; }
   const int slot = (int)bj;
   const float wnew = chunk_weight(hs, G);
-  {
-    const int j0 = base + kFinVec * tid;
+#pragma unroll
+  for (int r = 0; r < kFinVec; ++r)
+    if (j0 + r == slot) sa[r] = wnew;
+  if (sc16 && j0 < M) {
+    *reinterpret_cast<f32x4*>(sc + j0) = sa;
+  } else {
 #pragma unroll
     for (int r = 0; r < kFinVec; ++r)
-      if (j0 + r == slot) sa[r] = wnew;
-    if (sc16 && j0 < M) {
-      *reinterpret_cast<f32x4*>(sc + j0) = sa;
-    } else {
-#pragma unroll
-      for (int r = 0; r < kFinVec; ++r)
-        if (j0 + r < M) sc[j0 + r] = sa[r];
-    }
-  }
-  if (slot < base) {
-    // (more than one pass) the slot's accumulated score was stored with an
-    // earlier pass: every thread's stores complete before it is replaced
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    __syncthreads();
-    if (tid == 0) sc[slot] = wnew;
+      if (j0 + r < M) sc[j0 + r] = sa[r];
   }
   if (tid == 0) {
     w[M] = wnew;
@@ -1122,7 +1094,7 @@ hipError_t launch_finish(const Shape& s, const Plan& p, bool out_too, int ns, co
                          void* kc, void* vc, const void* kn, const void* vn, void* out,
                          float* lse, float* wsum, float* scores, int32_t* token_pos,
                          int32_t* evict_idx, int32_t pos0, char* ws, float c, hipStream_t st) {
-  if (s.M > kFinPass) {
+  if (s.M > kFinSlots) {
     const hipError_t e = launch_combine(s, p, ns, q, kn, vn, out_too ? out : nullptr, lse, wsum,
                                         scores, nullptr, true, ws, c, st);
     if (e != hipSuccess) return e;

@@ -184,7 +184,9 @@ hipError_t launch_sdpa_decode(const Shape& s, const Plan& p, const void* q, cons
                               float* lse, float* wsum, char* ws, float scale, KeyPos kp,
                               hipStream_t st, float* scores_acc = nullptr);
 // T == 1, one call for the whole step: split kernel, then one block per head
-// merges the splits, accumulates the scores, picks the slot and inserts.
+// merges the splits, accumulates the scores, picks the slot and inserts (a
+// second block per head writes out and lse); above 4,096 slots the combine over
+// all CUs, then one wave per head that picks and inserts.
 hipError_t launch_decode_step(const Shape& s, const Plan& p, const void* q, void* kc, void* vc,
                               const void* kn, const void* vn, void* out, float* lse,
                               float* wsum, float* scores, int32_t* token_pos, int32_t* evict_idx,
