@@ -274,6 +274,8 @@ Plan path_plan(const Shape& s, int path, size_t max_bytes = SIZE_MAX) {
     off = align256(off + BH * s.G() * (size_t)((s.M + 3) & ~3) * sizeof(float));
     p.off_parts = off;   // sink for the logit stores of masked slots (64 lanes x 16 B)
     off = align256(off + 64 * 16);
+    p.off_keys = off;
+    off = align256(off + decode_candidate_bytes(s.BH(), s.M));
     p.bytes = off;
     return p;
   } else if (path == 3) {

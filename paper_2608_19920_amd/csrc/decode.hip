@@ -654,8 +654,9 @@ __device__ __forceinline__ bool lex_less(uint32_t ka, uint32_t ja, uint32_t kb, 
 // With scores non-null each slot's summed weight is added to its score, one
 // float32 addition; with ins_idx non-null the head's slot ins_idx[bh] (just
 // inserted, by the fused insert-first split) takes 0 + wsum[j] instead.
-// CAND: the block also leaves the (key, slot)-smallest of its updated scores
-// in the first two logits of its slots, which it alone has read.
+// CAND: the block also leaves the (key, slot)-smallest of its updated scores in
+// cand[bh][x]. (The partials and logits stay as the split left them, so the evict
+// half of a step reads the same inputs however often it is called.)
 // Bound by latency (statistics, then exp2 and the stores). Blocks of 1,024
 // threads with one slot each, out written by a block that also had slots:
 // 13.2 us at B4 Hkv8 G4 M32768, 7.0 like this (256 or 1,024 threads: 7.4, 7.3).
@@ -664,10 +665,10 @@ constexpr int kCombSlots = 4 * kCombThreads;
 template <int D, int G, bool CAND>
 __global__ __launch_bounds__(kCombThreads) void decode_combine(
     const bf16_t* __restrict__ q, const bf16_t* __restrict__ kn, const bf16_t* __restrict__ vn,
-    int Hq, int Hkv, int M, int nx, int nsplit, float c_log2, float* __restrict__ logits,
+    int Hq, int Hkv, int M, int nx, int nsplit, float c_log2, const float* __restrict__ logits,
     const float2* __restrict__ dstat, const float* __restrict__ dO, bf16_t* __restrict__ out,
     float* __restrict__ lse, float* __restrict__ wsum, float* __restrict__ scores,
-    const int32_t* __restrict__ ins_idx) {
+    const int32_t* __restrict__ ins_idx, uint2* __restrict__ cand) {
   constexpr int NT = kCombThreads;
   __shared__ HeadStats hs;
   __shared__ uint32_t red_k[NT / 64], red_j[NT / 64];
@@ -689,7 +690,7 @@ __global__ __launch_bounds__(kCombThreads) void decode_combine(
     return;
   }
   const int pitch = logit_pitch(M), c0 = blockIdx.x * kCombSlots, j0 = c0 + 4 * tid;
-  float* lgb = logits + bh * (size_t)G * pitch;
+  const float* lgb = logits + bh * (size_t)G * pitch;
   float* sc = scores ? scores + bh * (size_t)M : nullptr;
   const bool sc16 = (M & 3) == 0;     // score rows start 16-byte aligned
   f32x4 lg[G], sv = {0.f, 0.f, 0.f, 0.f};
@@ -744,7 +745,7 @@ __global__ __launch_bounds__(kCombThreads) void decode_combine(
     if (tid == 0) {
       for (int v = 1; v < NT / 64; ++v)
         if (lex_less(red_k[v], red_j[v], bk, bj)) { bk = red_k[v]; bj = red_j[v]; }
-      *reinterpret_cast<uint2*>(lgb + c0) = make_uint2(bk, bj);
+      cand[bh * (size_t)nx + blockIdx.x] = make_uint2(bk, bj);
     }
   }
 }
@@ -753,12 +754,11 @@ __global__ __launch_bounds__(kCombThreads) void decode_combine(
 // the smallest of the blocks' candidates and inserts the chunk there.
 __global__ __launch_bounds__(64) void decode_insert(
     bf16_t* __restrict__ kc, bf16_t* __restrict__ vc, const bf16_t* __restrict__ kn,
-    const bf16_t* __restrict__ vn, int G, int D, int M, const float* __restrict__ logits,
+    const bf16_t* __restrict__ vn, int D, int M, int nx, const uint2* __restrict__ cand,
     const float* __restrict__ wsum, float* __restrict__ scores, int32_t* __restrict__ token_pos,
     int32_t* __restrict__ evict_idx, int32_t pos0) {
   const size_t bh = blockIdx.x;
   const int lane = threadIdx.x;
-  const float* cand = logits + bh * (size_t)G * logit_pitch(M);
   const float wnew = wsum[bh * (size_t)(M + 1) + M];
   const bool copy = lane < D / 8;
   u32x4 krow = {0u, 0u, 0u, 0u}, vrow = krow;
@@ -767,8 +767,8 @@ __global__ __launch_bounds__(64) void decode_insert(
     vrow = load16(vn + bh * D + 8 * lane);
   }
   uint32_t bk = 0xFFFFFFFFu, bj = 0u;
-  for (int x = lane; x * kCombSlots < M; x += 64) {
-    const uint2 c = *reinterpret_cast<const uint2*>(cand + (size_t)x * kCombSlots);
+  for (int x = lane; x < nx; x += 64) {
+    const uint2 c = cand[bh * (size_t)nx + x];
     if (lex_less(c.x, c.y, bk, bj)) { bk = c.x; bj = c.y; }
   }
   wave_argmin(bk, bj);
@@ -987,6 +987,9 @@ hipError_t launch_split(hipStream_t st, int BH, const void* q, const void* kc, c
 }  // namespace
 
 int decode_max_split() { return kMaxSplit; }
+size_t decode_candidate_bytes(int BH, int M) {
+  return M > kFinSlots ? (size_t)BH * ((M + kCombSlots - 1) / kCombSlots) * sizeof(uint2) : 0;
+}
 
 // The decode kernels are instantiated for d = 64 and 128 and every group of 1
 // to 8 query heads. (The prefill kernels, which take the rest, pad the G rows
@@ -1043,9 +1046,9 @@ hipError_t launch_combine(const Shape& s, const Plan& p, int ns, const void* q, 
     auto go = [&](auto kern) {
       return launch_kernel(K_DECODE_COMBINE, kern, grid, dim3(kCombThreads), st, (const bf16_t*)q,
                            (const bf16_t*)kn, (const bf16_t*)vn, s.Hq, s.Hkv, s.M, nx, ns, c,
-                           (float*)(ws + p.off_logits), (const float2*)(ws + p.off_stats),
+                           (const float*)(ws + p.off_logits), (const float2*)(ws + p.off_stats),
                            (const float*)(ws + p.off_opart), (bf16_t*)out, lse, wsum, scores,
-                           ins_idx);
+                           ins_idx, (uint2*)(ws + p.off_keys));
     };
     return cand ? go(decode_combine<d.value, g.value, true>)
                 : go(decode_combine<d.value, g.value, false>);
@@ -1099,9 +1102,9 @@ hipError_t launch_finish(const Shape& s, const Plan& p, bool out_too, int ns, co
                                         scores, nullptr, true, ws, c, st);
     if (e != hipSuccess) return e;
     return launch_kernel(K_DECODE_INSERT, decode_insert, dim3(s.BH()), dim3(64), st, (bf16_t*)kc,
-                         (bf16_t*)vc, (const bf16_t*)kn, (const bf16_t*)vn, s.G(), s.d, s.M,
-                         (const float*)(ws + p.off_logits), (const float*)wsum, scores, token_pos,
-                         evict_idx, pos0);
+                         (bf16_t*)vc, (const bf16_t*)kn, (const bf16_t*)vn, s.d, s.M,
+                         (s.M + kCombSlots - 1) / kCombSlots, (const uint2*)(ws + p.off_keys),
+                         (const float*)wsum, scores, token_pos, evict_idx, pos0);
   }
   auto go = [&](auto kern) {
     return launch_kernel(K_DECODE_FINISH, kern, dim3(out_too ? 2 * s.BH() : s.BH()),

@@ -116,7 +116,8 @@ struct Plan {
   size_t off_parts;    // float colsum partials [nparts][BH][Nk]; decode: 1 KiB store sink
   size_t off_opart;    // float O partials [nsplit][BH][R][d] (nsplit > 1)
   size_t off_logits;   // decode: float logits [BH][G][Nk]
-  size_t off_keys;     // float accumulated scores [BH][M], the ranking copy of a chunk step
+  size_t off_keys;     // float accumulated scores [BH][M], the ranking copy of a chunk step;
+                       // decode: the combine blocks' eviction candidates
   size_t bytes;
 };
 // The plan of the least time whose workspace fits max_bytes; where none fits, the
@@ -125,6 +126,7 @@ Plan make_plan(const Shape& s, int dtype, size_t max_bytes = SIZE_MAX);
 constexpr int kMaxLseSplit = 16;  // key-range splits of the MFMA lse pass, at most
 int mfma_rows_per_wave();        // packed rows per wave of the MFMA kernels
 int decode_max_split();      // largest split-block count per head of the decode kernels
+size_t decode_candidate_bytes(int BH, int M);   // eviction candidates of a token step
 bool decode_supports(int d, int G);   // (d, G) pairs the decode kernels handle
 
 // ------------------------------------------------------------ kernel timing
