@@ -93,8 +93,10 @@ typedef enum {
 } h2o_policy;
 
 /* Bytes of device scratch h2o_sdpa_chunk needs for this shape (0 on invalid
- * arguments). The workspace holds partial row statistics and per-row-tile
- * partial column sums; its contents on entry are ignored. */
+ * arguments). The workspace holds partial row statistics, per-row-tile partial
+ * column sums and, where the keys are split, partial outputs; its contents on
+ * entry are ignored. The size follows the plan the call takes: it need not grow
+ * with the shape, and it differs between versions of the library. */
 size_t h2o_workspace_bytes(int B, int Hq, int Hkv, int T, int M, int d,
                            int dtype);
 

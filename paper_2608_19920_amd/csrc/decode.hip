@@ -191,7 +191,7 @@ struct InsArgs {
 // the rest of a longer row in rounds of as many. Rows of M % 4 != 0 slots, whose
 // starts are not 16-byte aligned, are read by single loads. (One load in flight per
 // thread past the first 4,096 slots made M = 32768 wait 112 times: the step
-// at B4 Hkv8 d128 166 us, 127 now.)
+// at B4 Hkv8 d128 166 us, 127 with these and 118 with non-temporal K and V loads.)
 constexpr int kScVec = 4;
 struct ScoreScan {
   static constexpr int kSlots = 4 * kScVec * kThreads;   // slots per round
@@ -927,7 +927,8 @@ __global__ __launch_bounds__(kFinThreads) void decode_finish(
 
 // Split blocks per head such that all blocks of the grid are resident at
 // once (blocks per CU of this kernel instance x CUs), at most kMaxSplit and
-// at most one wave per step of slots.
+// at most one wave per step of slots. (The non-temporal kernels take the same
+// registers and LDS, so the same count.)
 template <int D, int G, bool CACHE, bool INS = false>
 int split_count(int M, int BH) {
   static int resident = 0;
@@ -953,12 +954,18 @@ int split_count(int M, int BH) {
 
 // K and V bytes of a call from which its loads are non-temporal. A cache is read
 // once per call, in full: what of it should stay in the 256 MB Infinity Cache
-// depends on what else the caller's step reads, which is not known here, so a
-// call leaves that to the hardware until three such caches no longer fit.
-// Measured on three caches in turn (default / nt, us a step, G = 4): B10 M4096 d64
-// (84 MB) 23.4 / 26.0, B12 (101 MB) 30.2 / 29.1, B24 55.0 / 52.7; B4 Hkv8 d128 M32768
-// (537 MB) 124.5 / 117.2, insert-first 127 / 119; B8 Hkv16 d128 M16384 (1.07 GB)
-// 217 / 195.
+// depends on how many such caches the caller's program goes round, which a call
+// does not know. A model has one per layer, so the line lies where three no
+// longer fit. Non-temporal against default loads, rotations of 1 / 2 / 3 / 8 / 32
+// caches in graph replays, token step at B8 Hkv8 G4 d128 (change in time, %):
+//    64 MiB  +11 / +13 /  +7 /  -6 /  -5     192 MiB  +14 / -12 / -12 / -12
+//    96 MiB  +10 / +13 /  -5 /  -8 /  -6     256 MiB  +11 / -11 / -11 / -12
+//   128 MiB  +16 / +15 / -10 / -12 / -10     320 MiB   -9 / -12;  512 MiB -13 / -12
+// (d64: 128 MiB +20 / . / -7 / -10; insert-first, d128: +19 / . / -9 / -10.) A
+// program of one layer loses up to 16 % (24 % at d = 64) between the line and the
+// 288 MiB from which one cache does not fit either, one of two layers up to 15 %
+// below 192 MiB; every other gains. From 288 MiB on nobody would lose, and every
+// model below would give up the 5 to 12 %.
 constexpr size_t kNtBytes = size_t(96) << 20;
 
 // ins.scores non-null: the fused insert-first form (cache mode).
@@ -994,7 +1001,7 @@ size_t decode_candidate_bytes(int BH, int M) {
 // The decode kernels are instantiated for d = 64 and 128 and every group of 1
 // to 8 query heads. (The prefill kernels, which take the rest, pad the G rows
 // of a head to 128: GQA 7:1 at B2 Hkv4 d128 M16384 84 us a step
-// there, 25 here.)
+// there, 21.6 here.)
 bool decode_supports(int d, int G) { return (d == 64 || d == 128) && G >= 1 && G <= kMaxG; }
 
 namespace {

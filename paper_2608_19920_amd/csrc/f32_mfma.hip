@@ -20,8 +20,8 @@
 // What bounds it: the matrix cores (32 cycles per 16x16x4 product; a step of
 // 16 keys and 16 rows is 2 d/4 products forward, against 4 exponentials per
 // lane), so probabilities take the full-accuracy expf. At B1 Hq16 Hkv4 d64
-// M2048 T256 the attention takes 59 us, dq 56 and dk/dv 75 us, with the matrix
-// cores busy 40 % of the time (operand reads through L1 and a grid of 1 to 2.25
+// M2048 T256 the attention takes 60 us, dq 57 and dk/dv 76 us, with the matrix
+// cores busy 33 to 46 % of the time (operand reads through L1 and a grid of 1 to 2.25
 // blocks per CU take the rest); the scalar kernels of sdpa_generic.hip and
 // backward.hip take 5,010, 818 and 835 us.
 #include "internal.h"
